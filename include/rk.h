@@ -215,7 +215,10 @@ int rk_last_fill_ms(rk_chain *c, float *ms, int32_t *launches);
 
 /*
  * Kernel-level timing (for benchmarks; mode 0, off, by default).  In mode 1 or 2 the
- * fill launches its kernels one by one instead of replaying a graph, and the runtime
+ * fill runs by levels of diagonals (band products, mid products and a finalize per span
+ * length: how chains with the saving sweep are always filled; other chains are otherwise
+ * filled by square tiles of spans, one kernel per level), launches its kernels one by one
+ * instead of replaying a graph, and the runtime
  * records a pair of HIP events with every dispatch, at the kernel's start and end
  * (hipExtLaunchKernelGGL), so a launch's time is the kernel's own.  Mode 2 also runs
  * the counting variants of the fill kernels, which add up on the device the candidates

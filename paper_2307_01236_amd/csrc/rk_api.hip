@@ -57,6 +57,8 @@ struct rk_chain {
     int64_t bt_fill = -1;        // the solve whose schedule d_ops holds
     int64_t bt_res[3] = {0, 0, 0};
     int64_t *d_res = nullptr;
+    int32_t *host = nullptr;  // pinned: Tables::host
+    bool tiled = false;       // the last fill ran by tiles (its answer is in host[0])
     int16_t *d_argrow = nullptr;
     int32_t d_argrow_cap = 0;
 };
@@ -138,7 +140,7 @@ int ensure_device(rk_chain *c)
     const int32_t L = c->h.L, K = c->run.k_run;
     const bool sweep = !c->h.refwd.empty();
     const size_t nx = L + 1, nk = (size_t)L * K, nl = (size_t)L * L, nr = (size_t)rk::n_rows(L);
-    const size_t total = nx + 3 * nk + L + 2 * nl + nr + (sweep ? nk + nl : 0);
+    const size_t total = 4 * nk + nx + 3 * nk + L + 2 * nl + 2 * nr + (sweep ? nk + nl : 0);
     HIPCHK(hipMalloc(&c->d_chain, total * sizeof(int32_t)));
     int32_t *p = static_cast<int32_t *>(c->d_chain);
     size_t off = 0;
@@ -149,8 +151,20 @@ int ensure_device(rk_chain *c)
                    ? dst
                    : nullptr;
     };
+    std::vector<int32_t> opt4(4 * nk, 0);
+    int64_t reach = 0;
+    for (size_t j = 0; j < nk; ++j) {
+        opt4[4 * j] = c->run.xbar[j];
+        opt4[4 * j + 1] = c->run.c1[j];
+        opt4[4 * j + 2] = c->run.need1[j];
+        opt4[4 * j + 3] = (int32_t)std::min<int64_t>(4 * (int64_t)c->run.xbar[j], INT32_MAX);
+        reach = std::max<int64_t>(reach, c->run.xbar[j]);
+    }
+    for (int32_t v : c->h.x) reach = std::max<int64_t>(reach, v);
+    c->dc.reach = (int32_t)std::min<int64_t>(reach, 1 << 30);
     c->dc.L = L;
     c->dc.K = K;
+    c->dc.opt4 = put(opt4);  // first: 16-byte aligned
     c->dc.x = put(c->h.x);
     c->dc.xbar = put(c->run.xbar);
     c->dc.c1 = put(c->run.c1);
@@ -159,6 +173,7 @@ int ensure_device(rk_chain *c)
     c->dc.P = put(c->h.P);
     c->dc.need2 = put(c->h.need2);
     c->dc.lb = put(c->h.lb);
+    c->dc.msa = put(c->h.msa);
     c->dc.c3 = sweep ? put(c->run.c3) : nullptr;
     c->dc.need3 = sweep ? put(c->h.need3) : nullptr;
     c->dc.h_msa = c->h.msa.data();
@@ -167,7 +182,7 @@ int ensure_device(rk_chain *c)
     for (int32_t v : c->run.xbar) xbar_max = std::max<int64_t>(xbar_max, v);
     c->dc.xbar_halo = xbar_max > rk::HMAX ? rk::HMAX + 1 : rk::round64(xbar_max);
     if (!c->dc.x || !c->dc.xbar || !c->dc.c1 || !c->dc.need1 || !c->dc.need1max || !c->dc.P ||
-        !c->dc.need2 || !c->dc.lb || (sweep && (!c->dc.c3 || !c->dc.need3))) {  // leave no half-uploaded arrays behind: the next solve uploads again
+        !c->dc.need2 || !c->dc.lb || !c->dc.msa || !c->dc.opt4 || (sweep && (!c->dc.c3 || !c->dc.need3))) {  // leave no half-uploaded arrays behind: the next solve uploads again
         (void)hipFree(c->d_chain);
         c->d_chain = nullptr;
         return RK_E_DEVICE;
@@ -178,6 +193,10 @@ int ensure_device(rk_chain *c)
     if (!c->own_stream) HIPCHK(hipStreamCreateWithFlags(&c->own_stream, hipStreamNonBlocking));
     if (!c->d_res && hipMalloc(&c->d_res, 4 * sizeof(int64_t)) != hipSuccess) {
         c->d_res = nullptr;
+        return RK_E_NOMEM;
+    }
+    if (!c->host && hipHostMalloc(&c->host, 2 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+        c->host = nullptr;
         return RK_E_NOMEM;
     }
     return RK_OK;
@@ -237,6 +256,13 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
     if (c->prof.count && !c->prof.d_ctr)
         HIPCHK(hipMalloc(&c->prof.d_ctr, rk::CTR_WORDS * sizeof(unsigned long long)));
     c->tb.ctr = c->prof.count ? c->prof.d_ctr : nullptr;
+    c->tb.host = c->host;
+    // the saving sweep and profiled fills run by levels of diagonals
+    c->tiled = !c->dc.c3 && !c->prof.on;
+    auto launch = [&]() {
+        return c->tiled ? rk::launch_tiles(c->dc, c->tb, M - c->h.x[0], stream, &c->launches)
+                        : rk::launch_fill(c->dc, c->tb, stream, &c->launches, &c->prof);
+    };
     c->tb.rec = nullptr;  // the fill points it at the profiler's records per launch (mode 2)
     c->prof.ctr_valid = c->prof.count;
     c->stream = stream;
@@ -248,7 +274,7 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
                         c->g_prof == c->prof.on;
     if (direct) {
         c->prof.reset(stream);
-        HIPCHK(rk::launch_fill(c->dc, c->tb, stream, &c->launches, &c->prof));
+        HIPCHK(launch());
     } else if (replay) {
         HIPCHK(hipGraphLaunch(c->gexec, stream));
     } else {
@@ -263,7 +289,7 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
         if (!c->prof.on && hipStreamIsCapturing(stream, &cs) == hipSuccess &&
             cs == hipStreamCaptureStatusNone &&
             hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-            const hipError_t le = rk::launch_fill(c->dc, c->tb, stream, &c->launches, &c->prof);
+            const hipError_t le = launch();
             hipGraph_t graph = nullptr;
             const hipError_t ce = hipStreamEndCapture(stream, &graph);
             if (le == hipSuccess && ce == hipSuccess && graph &&
@@ -282,7 +308,7 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
         } else {  // the stream is being captured by the caller, or capture is unavailable
             c->gexec = nullptr;
             c->prof.reset(stream);
-            HIPCHK(rk::launch_fill(c->dc, c->tb, stream, &c->launches, &c->prof));
+            HIPCHK(launch());
         }
     }
     if (!c->in_caller_graph) HIPCHK(hipEventRecord(c->ev_fill1, stream));
@@ -295,7 +321,9 @@ int answer(rk_chain *c, int32_t *out)
 {
     if (!c->queued) return RK_E_NOT_SOLVED;
     HIPCHK(wait_fill(c));
+    if (c->tiled && c->host[1]) return RK_E_INTERNAL;
     if (c->M < c->h.x[0]) { *out = RK_INF; return RK_OK; }
+    if (c->tiled) { *out = to_abi(c->host[0]); return RK_OK; }
     int32_t v = 0;
     const int64_t idx = rk::row_of(c->h.L, 0, c->h.L - 1) * c->tb.stride + c->tb.padl + (c->M - c->h.x[0]);
     HIPCHK(hipMemcpy(&v, c->tb.opt + idx, sizeof(int32_t), hipMemcpyDeviceToHost));
@@ -361,6 +389,7 @@ void rk_chain_destroy(rk_chain *c)
         if (c->own_ws) (void)hipFree(c->own_ws);
         if (c->d_ops) (void)hipFree(c->d_ops);
         if (c->d_res) (void)hipFree(c->d_res);
+        if (c->host) (void)hipHostFree(c->host);
         if (c->d_argrow) (void)hipFree(c->d_argrow);
         if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
         if (c->ev_fill0) (void)hipEventDestroy(c->ev_fill0);
@@ -513,6 +542,7 @@ int rk_read_row(rk_chain *c, int32_t s, int32_t t, int32_t *opt_row, int16_t *ar
     DeviceScope ds(c);
     if (!ds.ok) return RK_E_DEVICE;
     HIPCHK(wait_fill(c));
+    if (c->tiled && c->host[1]) return RK_E_INTERNAL;
     const int64_t base = rk::row_of(c->h.L, s, t) * c->tb.stride + c->tb.padl;
     if (opt_row) {
         HIPCHK(hipMemcpy(opt_row, c->tb.opt + base, (size_t)c->W * sizeof(int32_t), hipMemcpyDeviceToHost));
@@ -548,6 +578,7 @@ int rk_tradeoff_curve(rk_chain *c, int32_t *times, int64_t n)
     DeviceScope ds(c);
     if (!ds.ok) return RK_E_DEVICE;
     HIPCHK(wait_fill(c));
+    if (c->tiled && c->host[1]) return RK_E_INTERNAL;
     // budget b leaves b - x_0 slots beyond the chain input: Opt(0, L-1, b - x_0)
     const int64_t x0 = c->h.x[0], lead = std::min<int64_t>(n, x0);
     for (int64_t b = 0; b < lead; ++b) times[b] = RK_INF;

@@ -91,6 +91,9 @@ struct DevChain {
     const int32_t *c3;
     const int32_t *need3;
     const int32_t *h_msaH;  // [L(L+1)/2], host memory: from msaH(s,t) on, H(s,t) = lb(s,t) + P[s][s+1]
+    const int32_t *msa;    // [L(L+1)/2]  h_msa on the device
+    const int32_t *opt4;   // [L*K][4]  xbar, c1, need1, 4 xbar of an option together
+    int32_t reach;         // how far left of a column its cell reads: max of xbar and x
     int32_t xbar_halo;     // round64(max xbar): how far left case 1 reads from column m
 };
 
@@ -115,6 +118,9 @@ struct Tables {
     // 0 if its lower bound skipped it.
     unsigned long long *ctr;
     int32_t *rec;
+    // Pinned host memory that the tiled fill writes: [0] the answer Opt(0, L-1, M - x_0), [1]
+    // whether the fill failed (a wait that gave up).
+    int32_t *host;
 };
 
 // The finalize skip counter: a workgroup adds into slot blockIdx.x % CTR_SLOTS, the slots
@@ -175,6 +181,8 @@ extern const char *const kFillKernelNames[KFILL_NKINDS];
 // Launchers (rk_kernels.hip).  All return hipError_t of the launch.
 hipError_t launch_fill(const DevChain &ch, const Tables &tb, hipStream_t stream, int32_t *launches,
                        Profiler *prof);
+// The fill by square tiles (rk_tile.hip); m_ans: the answer's column (-1: none).
+hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hipStream_t stream, int32_t *launches);
 hipError_t launch_arg_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, int16_t *out,
                           hipStream_t stream);
 // Alg. 3 on the device; res[0] = number of steps, res[1] = index of the first

@@ -12,12 +12,11 @@
 // time and validity folded in.  Which choice realises a minimum is recomputed from
 // the finished table where it is needed (Alg. 3 does the same: it asks which case
 // attains Opt(s,t,m)), so the fill keeps no argmin bookkeeping.
-#include "rk_internal.h"
+#include "rk_device.h"
 
 #include <hip/hip_ext.h>
 
 #include <algorithm>
-#include <type_traits>
 
 namespace rk {
 
@@ -110,29 +109,6 @@ constexpr uint32_t OOB = 0x80000000u;
 
 
 // ---------------------------------------------------------------------------------------
-// Workgroups of a launch go to the 8 XCDs round-robin (id g to XCD g mod 8), and each XCD
-// has its own L2.  Tiles are laid out as column chunks x n_idx tiles per chunk, and XCD x
-// (g mod 8) takes the chunks x, x + 8, x + 16, ..., each with its n_idx tiles in order.
-// Every XCD then keeps whole column chunks (tiles that share operand rows share its L2, at
-// about the same time) and gets chunks from the whole budget range, so work that shrinks
-// with the budget column (tiles past the store-everything budget) stays even over the
-// XCDs.  Launches hold 8 ceil(n_chunks / 8) n_idx workgroups; *chunk >= n_chunks marks a
-// spare one.  Correctness does not depend on the dispatch order.
-// ---------------------------------------------------------------------------------------
-__device__ inline void chunk_tile(uint32_t g, uint32_t n_idx, int32_t *chunk, int32_t *idx)
-{
-    const uint32_t j = g / 8;
-    // scalars: the division is expanded with vector instructions, and without the hint
-    // every address derived from the tile would be computed (and loaded) per lane
-    *chunk = __builtin_amdgcn_readfirstlane((int32_t)(g % 8 + 8 * (j / n_idx)));
-    *idx = __builtin_amdgcn_readfirstlane((int32_t)(j % n_idx));
-}
-static inline uint32_t chunk_grid(int32_t n_chunks, int32_t n_idx)
-{
-    return (uint32_t)(8 * ((n_chunks + 7) / 8) * n_idx);
-}
-
-// ---------------------------------------------------------------------------------------
 // Band product.  For the spans d in [tau, tau + T) (one band), the part of Eq. fn over
 // the splits i whose two operands are older than the band (both s..i-1 and i..t shorter
 // than tau).  That is a min-plus product, elementwise in m:
@@ -159,19 +135,6 @@ static inline uint32_t chunk_grid(int32_t n_chunks, int32_t n_idx)
 // them stay inside the table with its slack rows.
 // ---------------------------------------------------------------------------------------
 __device__ inline uint32_t sat_add(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
-
-// Maximum of a 32-bit value over the 64 lanes of a wavefront (all lanes active): DPP
-// exchanges inside each row of 16 lanes, then the four row maxima read as scalars.
-__device__ inline uint32_t wave_max_u32(uint32_t v)
-{
-    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, false));   // quad_perm 1,0,3,2
-    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, false));   // quad_perm 2,3,0,1
-    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, false));  // row_ror 4
-    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, false));  // row_ror 8
-    const uint32_t r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
-    const uint32_t r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
-    return max(max(r0, r1), max(r2, r3));
-}
 
 // Splits of the band product's first pass, before it cuts its split range (see k_product).
 constexpr int32_t PROD_PREFIX = 40;
@@ -490,26 +453,9 @@ __global__ __launch_bounds__(NW * 64) void k_product(DevChain ch, Tables tb, int
 // loads are issued one split ahead of its relaxation.  Cells past the table are computed
 // and not stored (their operand rows are clamped into the table).
 // ---------------------------------------------------------------------------------------
-// Calls f(integral_constant<int, U>) for U = B .. E-1 in order: a loop unrolled by
-// construction, whose index is a compile-time constant in the body.
-template <int B, int E, typename F>
-__device__ inline void static_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
 // rows (group A) or ends (group B) of a mid product tile
 template <int WD>
 constexpr int mid_rows() { return 4; }
-
-// load at a byte offset from a wave-uniform base (one scalar base + one 32-bit lane offset)
-__device__ inline int32_t ldb(const int32_t *base, uint32_t byte_off)
-{
-    return *(const int32_t *)((const char *)base + byte_off);
-}
 
 // Returns false when the tile is skipped by its lower bound.  Always inlined: k_mid calls it
 // from three places, and an outlined call would need a scratch frame.
@@ -790,12 +736,6 @@ __device__ inline int32_t ldrow(const int32_t *base, uint32_t pitch, uint32_t by
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, (int)pitch, 0x00020000);
     return __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, 0);
 }
-
-// A store marked nontemporal: its line is the first the caches let go.  The finalize writes
-// several rows per cell that only later launches read, most of them on other XCDs; with
-// these stores so marked the fill measured 0.13 ms faster (0.33 ms with the saving sweep),
-// the products and mids included, which keep more of their operands in L2.
-__device__ inline void st_nt(int32_t v, int32_t *p) { __builtin_nontemporal_store(v, p); }
 
 // The arguments before the first aggregate are preloaded into SGPRs when a wave starts (the
 // library is built with kernarg preloading of up to 14 dwords): the three table pointers and
@@ -1462,7 +1402,7 @@ __device__ inline uint32_t wave_min_u32(uint32_t v)
 // sweep's validity and the saturation), its right operand from Opt at the shifted column;
 // an option's rest from Opt.  The activation sizes (and the options' xbar, when it fits)
 // are copied to LDS first, so no load waits on another.  Shifted columns are clamped into
-// the row's left pad: a candidate whose column would fall left of it is invalid.
+// the row's left pad: a candidate whose column would fall left of column 0 is invalid.
 constexpr int32_t BT_XBAR_LDS_MAX = 8192;  // xbar entries kept in LDS (32 KiB)
 // Frames on the stack: every step pushes at most 2 per block its span loses (case 3 pushes
 // 4 and loses at least 2 blocks).
@@ -1548,7 +1488,7 @@ __global__ __launch_bounds__(64) void k_backtrace(DevChain ch, Tables tb, int32_
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
                 const int32_t j = r * 64 * NB + 64 * u + lane;
-                take(j < d, (uint32_t)av[u] + (uint32_t)qv[u], (uint32_t)(s + 1 + j));
+                take(j < d && m >= xi[u], (uint32_t)av[u] + (uint32_t)qv[u], (uint32_t)(s + 1 + j));
             }
             take(o < K && m >= need, (uint32_t)c1 + (uint32_t)rest, (uint32_t)(L + o));
             if (sweep) {  // case 3 with option o: c3 + H(s+1, t, m - mem), mem = xbar - x_{s+1}

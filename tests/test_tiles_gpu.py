@@ -1,0 +1,81 @@
+"""The tiled fill (16 x 16 spans, 64 budgets per workgroup) at the sizes where it can go wrong,
+full tables against the oracle: chains around multiples of 16 blocks, budgets around multiples
+of 64 columns, and activation sizes and options that read up to just below, at and above the
+columns staged in LDS (0, 64, 128 and 192; unstaged beyond)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2307_01236_amd import rk
+from paper_2307_01236_amd.chaingen import make_random_chain
+from test_parity_gpu import full_parity, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L,M", [(1, 63), (2, 64), (15, 127), (16, 128), (17, 191), (31, 62), (32, 130), (33, 65),
+                                 (47, 256), (48, 100), (49, 320), (81, 200)])
+def test_tile_and_chunk_edges(L, M):
+    """Both triangular and square tiles, whole and cut; the last chunk full and ragged."""
+    ch = make_random_chain(600 + L, L, 1 + L % 6, allow_zero=L % 2 == 0, xmax=5, amax=9, tmax=4, tmin=0,
+                           small_times=L % 3 == 0)
+    full_parity(ch, M)
+
+
+@pytest.mark.parametrize("reach", [0, 1, 63, 64, 65, 128, 129, 192, 193])
+def test_reach_of_case_1(reach):
+    """The largest x + mem of an option decides how many columns left of a chunk are staged."""
+    ch = make_random_chain(700 + reach, 36, 5, xmax=max(1, reach // 3), amax=2 * reach // 3 + 1, tmax=9, tmin=0,
+                           allow_zero=True)
+    if reach == 0:
+        ch.x[:], ch.mem[:] = 0, 0
+    else:
+        ch.mem[:] = np.minimum(ch.mem, np.maximum(reach - ch.x[1:, None], 0))
+        s = int(np.argmin(ch.x[1:]))
+        ch.mem[s, 0] = reach - ch.x[s + 1]
+        assert int((ch.x[1:, None] + ch.mem).max()) == reach and ch.x.max() <= reach
+    full_parity(ch, 900)
+
+
+def test_splits_sorted_out_in_pieces():
+    """330 blocks: products of up to 305 splits, whose list of splits that matter is made in
+    three pieces.  The fill by levels of diagonals (profiled solves) on the other side."""
+    ch = make_random_chain(8123, 330, 2, M=420, xmax=2, amax=4, tmax=2, tmin=0)
+    s, t = rk.Solver(ch), rk.Solver(ch)
+    try:
+        a = s.solve()
+        ops, _ = s.schedule()
+        ok, tm, pk, _ = oracle.simulate(ch, ops)
+        assert ok and tm == a and pk <= ch.M
+        t.set_profiling(1)  # the fill by levels of diagonals
+        assert t.solve() == a
+        assert np.array_equal(s.tradeoff_curve(), t.tradeoff_curve())
+        for i in (0, 100, 250, 329):
+            for j in range(i, 330, 13):
+                for x, y in zip(s.row(i, j), t.row(i, j)):
+                    assert np.array_equal(x, y), (i, j)
+    finally:
+        s.close()
+        t.close()
+
+
+def test_two_chains_at_once_on_two_streams():
+    """Two fills in flight at the same time, each waiting for its own workgroups only."""
+    import torch
+    chains = [make_random_chain(31, 70, 4, xmax=9, amax=30, tmax=9), make_random_chain(32, 90, 3, xmax=7, amax=20, tmax=5)]
+    want = [oracle.solve(c) for c in chains]
+    solvers = [rk.Solver(c) for c in chains]
+    try:
+        ws = [torch.empty(s.workspace_bytes(c.M), dtype=torch.uint8, device="cuda:0") for s, c in zip(solvers, chains)]
+        st = [torch.cuda.Stream() for _ in chains]
+        for rep in range(5):
+            say(f"  round {rep}")
+            for s, c, w, q in zip(solvers, chains, ws, st):
+                s.solve_async(c.M, w.data_ptr(), w.numel(), q.cuda_stream)
+            for s, sol in zip(solvers, want):
+                assert s.result() == sol.answer
+        for s, sol in zip(solvers, want):
+            assert np.array_equal(s.rows(want_arg=False)[0], sol.rows()[0])
+    finally:
+        for s in solvers:
+            s.close()
