@@ -202,7 +202,8 @@ int ensure_device(rk_chain *c)
     return RK_OK;
 }
 
-int32_t to_abi(int32_t v) { return v >= DINF ? RK_INF : v; }
+// an opt entry as the ABI shows it (opt entries carry the ONLY_CASE1 mark)
+int32_t to_abi(int32_t v) { return (v & DINF) == DINF ? RK_INF : v & DINF; }
 
 // Tables of rk_solve_noalloc: a static array on every device the library runs on.  In host
 // code its name stands for a host-side shadow, not for device memory: the device address

@@ -47,6 +47,11 @@ namespace rk {
 constexpr int32_t DINF = (1 << 30) - 1;
 static_assert(RK_TIME_LIMIT < DINF, "finite values must stay below the device infinity");
 
+// The tiled fill marks the opt entries whose value no split of case 2 reaches, only an option
+// of case 1, with one bit above the value (the fill by diagonals never does): Alg. 3 then need
+// not look at the splits there.  Readers of opt mask it off.
+constexpr int32_t ONLY_CASE1 = 1 << 30;
+
 // Spans per band: every band of BAND span lengths gets one tiled product over
 // the splits whose two operands are older than the band.  Inside a band, mid
 // products every MIDMIN spans cover the splits whose longer operand lies in the

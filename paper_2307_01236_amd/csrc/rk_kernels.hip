@@ -1311,7 +1311,7 @@ hipError_t launch_fill(const DevChain &ch, const Tables &tb, hipStream_t stream,
 // ---------------------------------------------------------------------------------------
 __device__ inline int32_t opt_at(const Tables &tb, int32_t L, int32_t s, int32_t t, int32_t m)
 {
-    return tb.opt[row_of(L, s, t) * tb.stride + tb.padl + m];
+    return tb.opt[row_of(L, s, t) * tb.stride + tb.padl + m] & DINF;  // (without ONLY_CASE1)
 }
 
 __device__ inline uint64_t split_key(const DevChain &ch, const Tables &tb, int32_t s, int32_t t,
@@ -1376,11 +1376,18 @@ hipError_t launch_arg_row(const DevChain &ch, const Tables &tb, int32_t s, int32
 }
 
 // ---------------------------------------------------------------------------------------
-// Alg. 3 (rk-Rotor-Build) with an explicit stack, one wavefront.  Every lane keeps the
-// same stack copy in LDS (all lanes write identical frames), so no barrier is needed;
-// the lanes share only the choice search at each visited cell.
+// Alg. 3 (rk-Rotor-Build) with an explicit stack, one workgroup.  The first wave holds the
+// state and decides; all waves fetch for it.  A visited cell costs a dependent round trip to
+// memory, so the rounds are few and wide:
+//  - a cell whose value only case 1 reaches (ONLY_CASE1) leads to row (s+1, t), usually another
+//    such cell.  One round brings the columns that up to BT_STEPS such steps can reach of rows
+//    s+1, s+2, .. and their options into LDS, and the first wave walks on from there;
+//  - at any other cell every candidate is evaluated, one per thread, and the smallest
+//    (cost, code) taken.
+// (One wave, all candidates of every cell: 1.7-2 us a cell.  Schedule kernel, before -> after,
+// at 128 blocks 200 -> 94 us, 384 blocks 804 -> 156 us, 1000 blocks 3.5 -> 1.85 ms.)
 // ---------------------------------------------------------------------------------------
-struct Frame { int32_t type, a, b, c; };  // type 0: Build(s=a, t=b, m=c); 1: emit (kind=a, block=b, option=c)
+struct Frame { int32_t type, a, b, c; };  // type 0: Build(s = a mod 2^11, t = a >> 11, m = b), opt entry c; 1: emit (kind=a, block=b, option=c)
 static_assert(sizeof(Frame) == 4 * sizeof(int32_t), "frames are four int32 in LDS");
 
 // Minimum of a 32-bit value over the 64 lanes of a wavefront (all lanes active): DPP
@@ -1397,137 +1404,258 @@ __device__ inline uint32_t wave_min_u32(uint32_t v)
     return min(min(r0, r1), min(r2, r3));
 }
 
-// Per visited cell, the lanes evaluate its candidates in parallel with one round of
-// independent loads: a split's left operand comes from ap (which already holds P, the
-// sweep's validity and the saturation), its right operand from Opt at the shifted column;
-// an option's rest from Opt.  The activation sizes (and the options' xbar, when it fits)
-// are copied to LDS first, so no load waits on another.  Shifted columns are clamped into
-// the row's left pad: a candidate whose column would fall left of column 0 is invalid.
-constexpr int32_t BT_XBAR_LDS_MAX = 8192;  // xbar entries kept in LDS (32 KiB)
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+constexpr int32_t BT_THREADS = 1024, BT_WAVES = BT_THREADS / 64;
+constexpr int32_t BT_SPLIT_WAVES = 12;          // waves that look at splits (the others: options)
+constexpr int32_t BT_STEPS = 24;                // most steps per round
+constexpr int32_t BT_WINDOW = 8192;             // words of rows that a round holds in LDS
+constexpr int32_t BT_LDS = 150 * 1024;          // LDS with the options of every block in it, at most
 // Frames on the stack: every step pushes at most 2 per block its span loses (case 3 pushes
 // 4 and loses at least 2 blocks).
 __host__ __device__ inline int32_t bt_stack_cap(const DevChain &ch) { return (ch.c3 ? 4 : 2) * ch.L + 8; }
-
-template <bool XBAR_LDS>
-__global__ __launch_bounds__(64) void k_backtrace(DevChain ch, Tables tb, int32_t m_top,
-                                                  rk_op *__restrict__ ops, int64_t cap,
-                                                  int64_t *__restrict__ res)
+// Steps per round: n steps reach n reach + 1 columns of n rows.  1: no window, every option's
+// word is fetched on its own (about 1 us a step; a round with its window takes as long as two).
+static int32_t bt_steps(const DevChain &ch)
 {
-    extern __shared__ int32_t sh[];
-    const int32_t lane = threadIdx.x, L = ch.L, K = ch.K;
+    int32_t n = 1;
+    while (n < BT_STEPS && (n + 1) * (((n + 1) * (int64_t)ch.reach + 64) / 64 * 64) <= BT_WINDOW) ++n;
+    return ch.c3 || n < 3 ? 1 : n;
+}
+
+template <bool OPTS_LDS>
+__global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb, int32_t m_top, int32_t steps,
+                                                          rk_op *__restrict__ ops, int64_t cap,
+                                                          int64_t *__restrict__ res)
+{
+    extern __shared__ __align__(16) int32_t sh[];
+    __shared__ i32x4 found[BT_WAVES];  // per wave: cost, code, entry of the next cell, entry of the left sub-span
+    __shared__ int32_t order[6];       // what the first wave wants: mode, s, t, m, steps, the cell's entry
+    const int32_t L = ch.L, K = ch.K, tid = (int32_t)threadIdx.x, lane = tid & 63;
+    const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t stack_cap = bt_stack_cap(ch);
     const bool sweep = ch.c3 != nullptr;
     Frame *const stk = reinterpret_cast<Frame *>(sh);
-    int32_t *const xs = sh + 4 * stack_cap;  // x_0..x_L
-    int32_t *const xbs = xs + (L + 1);
-    for (int32_t j = lane; j <= L; j += 64) xs[j] = ch.x[j];
-    if (XBAR_LDS)
-        for (int32_t j = lane; j < L * K; j += 64) xbs[j] = ch.xbar[j];
-    __syncthreads();
-    const int32_t *const xbar = XBAR_LDS ? xbs : ch.xbar;
+    // options of every block (xbar, r(F)+r(B), need1): in LDS where they fit
+    i32x4 *const lo = reinterpret_cast<i32x4 *>(sh + 4 * stack_cap);
+    int32_t *const win = sh + 4 * stack_cap + (OPTS_LDS ? 4 * L * K : 0);
+    int32_t *const xs = win + (steps > 1 ? BT_WINDOW : 0);  // x_0..x_L
+    int32_t *const fs = xs + L + 1;  // F(i) = P[0][i], the no-save forwards before block i
+    int32_t *const lbs = fs + L + 1; // lb(0, i-1): lb(s, t) = lbs[t+1] - lbs[s]
+    for (int32_t j = tid; j <= L; j += BT_THREADS) {
+        xs[j] = ch.x[j];
+        fs[j] = j < L ? ch.P[j] : 0;
+        lbs[j] = j ? ch.lb[j - 1] : 0;
+    }
+    if constexpr (OPTS_LDS)
+#pragma unroll 4
+        for (int32_t j = tid; j < L * K; j += BT_THREADS) lo[j] = ((const i32x4 *)ch.opt4)[j];
     const int64_t stride = tb.stride;
-    const int32_t padl = tb.padl;
-    int32_t sp = 0;
-    int64_t n = 0, nfwd = -1, status = 0;
+    const int32_t padl = tb.padl, X = ch.reach;
+    auto option = [&](int32_t j) -> i32x4 {
+        if constexpr (OPTS_LDS) return lo[j];
+        else return ((const i32x4 *)ch.opt4)[j];
+    };
+    auto entry = [&](int32_t s, int32_t t, int32_t m) { return tb.opt[row_of(L, s, t) * stride + padl + m]; };
+    const int32_t pieces = (steps * X + 64) / 64;  // of 64 columns per row of the window: m + 1 - 64 pieces .. m
 
+    // the first wave's state: the cell being resolved; the stack holds what comes after it
+    enum { DONE, WALK, SEARCH };
+    int32_t s = 0, t = L - 1, m = m_top, own = -1;  // own: opt entry of the cell (-1: not known yet)
+    int32_t sp = 0;
+    int64_t n = 0, nfwd = -1;
+    int32_t status = 0;
+    bool have = true;
     auto emit = [&](int32_t kind, int32_t block, int32_t option) {
-        if (kind == RK_BWD && nfwd < 0) nfwd = n;
         if (lane == 0 && n < cap) ops[n] = rk_op{kind, block, option};
         ++n;
     };
     auto push = [&](Frame f) { stk[sp] = f; ++sp; };
 
-    // The cell being resolved stays in registers; the stack holds what comes after it.
-    int32_t s = 0, t = L - 1, m = m_top;
-    bool have = true;
     for (;;) {
-        if (!have) {
-            if (sp == 0) break;
-            const Frame f = stk[--sp];
-            if (f.type == 1) { emit(f.a, f.b, f.c); continue; }
-            s = f.a; t = f.b; m = f.c;
+        int32_t mode = SEARCH, ns = 0;
+        if (wave == 0) {
+            while (!have && sp > 0) {  // emit the run of steps on top of the stack, or take its cell
+                const Frame f = stk[max(sp - 1 - lane, 0)];
+                const uint64_t cells = __ballot(lane < sp && f.type == 0);
+                const int32_t run = min(cells ? (int32_t)__builtin_ctzll(cells) : 64, sp);
+                if (lane < run && n + lane < cap) ops[n + lane] = rk_op{f.a, f.b, f.c};
+                const uint64_t bwd = __ballot(lane < run && f.a == RK_BWD);
+                if (nfwd < 0 && bwd) nfwd = n + __builtin_ctzll(bwd);
+                n += run;
+                sp -= run;
+                if (run == 0) {
+                    const int32_t a = __builtin_amdgcn_readfirstlane(f.a);
+                    s = a & 2047;
+                    t = a >> 11;
+                    m = __builtin_amdgcn_readfirstlane(f.b);
+                    own = __builtin_amdgcn_readfirstlane(f.c);
+                    --sp;
+                    have = true;
+                }
+            }
+            if (!have || status) mode = DONE;
+            else if (own >= 0 && (own & ONLY_CASE1)) mode = WALK;
+            ns = min(steps > 1 ? steps : 64, t - s + 1);
+            if (lane == 0) order[0] = mode, order[1] = s, order[2] = t, order[3] = m, order[4] = ns, order[5] = own;
         }
-        const int32_t d = t - s;
-        const int32_t own = tb.opt[row_of(L, s, t) * stride + padl + m];
-        // This lane's smallest (cost, code) key over its candidates: split i = s+1+j (j < d)
-        // has code i, option o has code L+o.  Addresses of candidates past the end are
-        // clamped into the tables; their values are then ignored.  Row numbers fit 32 bits
-        // (L <= 2000), so each address is one 32x32+64 multiply-add from the table base.
-        uint64_t best = ~0ull;
-        auto take = [&](bool ok, uint32_t v, uint32_t code) {
-            const uint64_t key = ok ? ((uint64_t)v << 32) | code : ~0ull;
-            best = key < best ? key : best;
-        };
-        auto row32 = [&](int32_t a, int32_t b) { return (uint32_t)(a * L - ((a * (a - 1)) >> 1) + b - a); };
-        const uint32_t ustride = (uint32_t)stride;
-        const int32_t *const ap_s = tb.ap + (uint64_t)row32(s, s) * ustride + padl + m;
-        const int32_t rest_row = row32(min(s + 1, t), t);
-        // NB split candidates per lane and round of loads: as many as the cell has splits
-        // (up to 8 per lane), so short spans do not pay for the longest ones
-        auto cell = [&](auto nbc) {
-        constexpr int NB = decltype(nbc)::value;
-        const int32_t rounds = max((d + 64 * NB - 1) / (64 * NB), (K + 63) / 64);
-        for (int32_t r = 0; r < rounds; ++r) {
-            // the option's xbar first: when it comes from global memory, the rest's address
-            // waits for it alone, not for the splits' loads
-            const int32_t o = r * 64 + lane, ko = s * K + min(o, K - 1);
-            const int32_t xb = xbar[ko];
-            int32_t xi[NB], av[NB], qv[NB];
+        __syncthreads();
+        auto ordered = [&](int32_t k) { return __builtin_amdgcn_readfirstlane(order[k]); };
+        mode = ordered(0);
+        if (mode == DONE) break;
+        const int32_t cs = ordered(1), ct = ordered(2), cm = ordered(3);
+        if (mode == WALK) {
+            const int32_t nr = ordered(4);
+            if (steps == 1) {
+                __syncthreads();  // (the first wave fetches as it walks)
+            } else {
+                // rows cs + 1 .. cs + nr (those of the span), 64 columns at a time; a wave's up to
+                // BT_WINDOW / BT_THREADS pieces are in flight together
+                const int32_t total = min(nr, ct - cs) * pieces;
+                int32_t v[BT_WINDOW / BT_THREADS];
 #pragma unroll
-            for (int u = 0; u < NB; ++u) xi[u] = xs[min(s + 1 + r * 64 * NB + 64 * u + lane, t)];
+                for (int32_t q = 0; q < BT_WINDOW / BT_THREADS; ++q) {
+                    const int32_t k = wave + BT_WAVES * q, j = k / pieces, c = cm + 1 - 64 * (pieces - k % pieces) + lane;
+                    // (left of column 0: any entry, never chosen)
+                    if (k < total) v[q] = tb.opt[row_of(L, cs + 1 + j, ct) * stride + padl + max(c, 0)];
+                }
 #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int32_t jc = min(r * 64 * NB + 64 * u + lane, max(d - 1, 0));
-                const int32_t i = min(s + 1 + jc, t);
-                av[u] = ap_s[(uint64_t)(uint32_t)jc * ustride];
-                qv[u] = tb.opt[(uint64_t)row32(i, t) * ustride + (uint32_t)(padl + m - min(xi[u], padl))];
+                for (int32_t q = 0; q < BT_WINDOW / BT_THREADS; ++q)
+                    if (wave + BT_WAVES * q < total) win[(wave + BT_WAVES * q) * 64 + lane] = v[q];
+                __syncthreads();
             }
-            const int32_t c1 = ch.c1[ko], need = ch.need1[ko];
-            const int32_t rest_v = tb.opt[(uint64_t)rest_row * ustride + (uint32_t)(padl + max(m - xb, -padl))];
-            const int32_t rest = t > s ? rest_v : 0;  // row (s, s) stands in when t == s
-#pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int32_t j = r * 64 * NB + 64 * u + lane;
-                take(j < d && m >= xi[u], (uint32_t)av[u] + (uint32_t)qv[u], (uint32_t)(s + 1 + j));
+        } else {
+            // this thread's smallest (cost, code) over its candidates: splits i = s+1+c, then options
+            uint64_t best = ~0ull;
+            int32_t next = 0, side = 0;
+            const int32_t d = ct - cs;
+            // A split costs at least lb(s,t) + P(s,i): where the cell's value is known, those that
+            // cost more by that alone are not looked at.
+            const int32_t known = ordered(5);
+            const int32_t most = known < 0 ? INT32_MAX : (known & DINF) - (lbs[ct + 1] - lbs[cs]);
+            if (known < 0 && tid == 0) order[5] = entry(cs, ct, cm);
+            auto take = [&](bool ok, uint32_t v, int32_t code, int32_t nx, int32_t sd) {
+                const uint64_t key = ok && v < (uint32_t)DINF ? (uint64_t)v << 32 | (uint32_t)code : ~0ull;
+                if (key < best) best = key, next = nx, side = sd;
+            };
+            // (all loads of a candidate in one round trip, at clamped addresses; rows (s, i-1) are
+            // consecutive, row (i, t) is row32(i) + t, below 2^32)
+            const uint32_t ustride = (uint32_t)stride;
+            const int32_t *const left = tb.opt + row_of(L, cs, cs) * stride + padl + cm;
+            const int32_t *const right = tb.opt + ct * stride + padl, *const below = tb.opt + row_of(L, min(cs + 1, ct), ct) * stride + padl;
+            auto row32 = [&](int32_t i) { return (uint32_t)(i * L - ((i * (i - 1)) >> 1) - i); };
+            // (splits and options on waves of their own, so that no wave waits for both)
+            if (wave < BT_SPLIT_WAVES) {
+                for (int32_t c = tid; c < d; c += 64 * BT_SPLIT_WAVES) {
+                    const int32_t i = cs + 1 + c, x = xs[i], p = fs[i] - fs[cs];
+                    if (p > most) continue;
+                    const int32_t need = ch.need2[cs * L + i];
+                    const int32_t l = left[(uint64_t)(uint32_t)c * ustride], r = right[(uint64_t)row32(i) * ustride + (uint32_t)max(cm - x, 0)];
+                    take(cm >= need && (l & DINF) < DINF && (r & DINF) < DINF,
+                         (uint32_t)(l & DINF) + (uint32_t)(r & DINF) + (uint32_t)p, i, r, l);
+                }
+            } else {
+                const int32_t *const hbelow = sweep ? tb.hopt + row_of(L, min(cs + 1, ct), ct) * stride + padl : below;
+                const int32_t x1 = xs[min(cs + 1, L)];
+                for (int32_t o = tid - 64 * BT_SPLIT_WAVES; o < K; o += BT_THREADS - 64 * BT_SPLIT_WAVES) {
+                    const i32x4 q = option(cs * K + o);
+                    const int32_t v = below[(uint32_t)max(cm - q.x, 0)];
+                    // case 3: c3 + H(s+1, t, m - mem), mem = xbar - x_{s+1}
+                    const int32_t h = sweep ? hbelow[(uint32_t)min(max(cm - (q.x - x1), 0), tb.W - 1)] : DINF;
+                    const int32_t c3 = sweep ? ch.c3[cs * K + o] : 0;
+                    const int32_t r = d > 0 ? v : 0;
+                    const bool ok = cm >= q.z;
+                    take(ok && (r & DINF) < DINF, (uint32_t)q.y + (uint32_t)(r & DINF), L + o, r, 0);
+                    if (d >= 2) take(ok && h < DINF, (uint32_t)c3 + (uint32_t)h, L + K + o, -1, 0);
+                }
             }
-            take(o < K && m >= need, (uint32_t)c1 + (uint32_t)rest, (uint32_t)(L + o));
-            if (sweep) {  // case 3 with option o: c3 + H(s+1, t, m - mem), mem = xbar - x_{s+1}
-                const int32_t hv =
-                    tb.hopt[(uint64_t)rest_row * ustride + (uint32_t)(padl + max(m - (xb - xs[s + 1]), 0))];
-                take(o < K && m >= need && t >= s + 2, (uint32_t)ch.c3[ko] + (uint32_t)hv, (uint32_t)(L + K + o));
-            }
+            const uint32_t bc = (uint32_t)(best >> 32), bk = (uint32_t)best;
+            const uint32_t cost = wave_min_u32(bc), code = wave_min_u32(bc == cost ? bk : ~0u);
+            if (bc == cost && bk == code) found[wave] = i32x4{(int32_t)cost, (int32_t)code, next, side};  // (no candidate: every lane the same)
+            __syncthreads();
         }
-        };
-        if (d <= 64) cell(std::integral_constant<int, 1>{});
-        else if (d <= 128) cell(std::integral_constant<int, 2>{});
-        else if (d <= 256) cell(std::integral_constant<int, 4>{});
-        else cell(std::integral_constant<int, 8>{});
-        const uint32_t bc = (uint32_t)(best >> 32), bk = (uint32_t)best;
-        const uint32_t cost = wave_min_u32(bc);
-        const uint32_t code = wave_min_u32(bc == cost ? bk : ~0u);
-        if (cost >= (uint32_t)DINF) { status = 1; break; }
-        if ((int32_t)cost != own) { status = 2; break; }
-        if (sp + 4 > stack_cap) { status = 3; break; }
+        if (wave != 0) continue;
+        if (mode == WALK) {
+            // per step the smallest option that reaches own, one option per lane; the step's
+            // operations are written after the walk, one step per lane
+            const int32_t s0 = s;
+            int32_t chosen = 0, j = 0;
+            const int32_t *row = win + (64 * pieces - 1 - m);  // row s + 1, at column 0
+            i32x4 p = option(s * K + min(lane, K - 1));
+            bool more = true;  // the cell is one to walk from
+            auto step = [&](uint64_t hit, int32_t o0, int32_t r) {  // the chosen option's, and on to row s + 1
+                const int32_t l = (int32_t)__builtin_ctzll(hit);
+                chosen = lane == j ? o0 + l : chosen;
+                ++j;
+                m -= __builtin_amdgcn_readlane(p.x, l);
+                own = __builtin_amdgcn_readlane(r, l);
+                s += 1;
+                more = j < ns && (own & ONLY_CASE1);
+            };
+            if (steps > 1 && K <= 64) {
+                const int32_t lc = min(lane, K - 1);
+                while (more && s < t) {
+                    const i32x4 p1 = option((s + 1) * K + lc);  // the next row's options, in flight meanwhile
+                    const int32_t r = row[m - p.x];  // in the window whether the option fits or not: xbar <= reach
+                    const uint64_t hit = __ballot(m >= p.z && p.y + (r & DINF) == (own & DINF));
+                    if (!hit) { status = 2; more = false; break; }
+                    step(hit, 0, r);
+                    row += 64 * pieces;
+                    p = p1;
+                }
+            }
+            while (more) {
+                const bool last = s == t;
+                int32_t o0 = 0, r = 0;
+                uint64_t hit = 0;
+                for (; o0 < K && !hit; o0 += 64) {
+                    p = option(s * K + min(o0 + lane, K - 1));
+                    const int32_t c = m - p.x;
+                    if (!last) r = steps > 1 ? row[c] : entry(s + 1, t, max(c, 0));
+                    hit = __ballot(m >= p.z && p.y + (r & DINF) == (own & DINF));
+                }
+                if (!hit) { status = 2; break; }
+                step(hit, o0 - 64, r);
+                row += 64 * pieces;
+            }
+            have = s <= t;
+            if (sp + j > stack_cap) { status = 3; continue; }
+            if (lane < j) {
+                if (n + lane < cap) ops[n + lane] = rk_op{RK_FWD_SAVE, s0 + lane, chosen};
+                stk[sp + lane] = Frame{1, RK_BWD, s0 + lane, chosen};
+            }
+            n += j;
+            sp += j;
+            continue;
+        }
+        const i32x4 f = found[min(lane, BT_WAVES - 1)];
+        const uint32_t bc = (uint32_t)f.x, bk = (uint32_t)f.y;
+        const uint32_t cost = wave_min_u32(bc), code = wave_min_u32(bc == cost ? bk : ~0u);
+        const int32_t wl = (int32_t)__builtin_ctzll(__ballot(bc == cost && bk == code));
+        const int32_t next = __builtin_amdgcn_readlane(f.z, wl), side = __builtin_amdgcn_readlane(f.w, wl);
+        have = false;
+        if (cost >= (uint32_t)DINF) { status = 1; continue; }
+        if ((int32_t)cost != (order[5] & DINF)) { status = 2; continue; }
+        if (sp + 4 > stack_cap) { status = 3; continue; }
         if (code >= (uint32_t)(L + K)) {
             // case 3: F_s^o keeps its data; the sweep s+1..i-1 to x_i, where i is H's choice at
             // (s+1, t, u = m - mem); then i..t, x_i dropped, x_{s+1} made again from the kept
             // data, s+1..i-1, and B_s^o
             const int32_t o = (int32_t)code - L - K, s1 = s + 1;
-            const int32_t xb = xbar[s * K + o];
+            const int32_t xb = option(s * K + o).x;
             const int32_t u = m - (xb - xs[s1]);
             const int32_t hown = tb.hopt[row_of(L, s1, t) * stride + padl + u];
-            const int32_t *const aq_s = tb.aq + (uint64_t)row32(s1, s1) * ustride + padl + u - min(xs[s1], padl);
+            const int32_t *const aq_s = tb.aq + row_of(L, s1, s1) * stride + padl + u - min(xs[s1], padl);
             uint64_t hb = ~0ull;
             for (int32_t j = lane; j < t - s1; j += 64) {  // split i = s1 + 1 + j, code i
                 const int32_t i = s1 + 1 + j;
-                const int32_t a = aq_s[(uint64_t)(uint32_t)j * ustride];
-                const int32_t q = tb.opt[(uint64_t)row32(i, t) * ustride + (uint32_t)(padl + u - min(xs[i], padl))];
+                const int32_t a = aq_s[j * stride];
+                const int32_t q = tb.opt[row_of(L, i, t) * stride + (padl + u - min(xs[i], padl))];
                 hb = min(hb, ((uint64_t)((uint32_t)a + (uint32_t)q) << 32) | (uint32_t)i);
             }
             const uint32_t hc = (uint32_t)(hb >> 32), hk = (uint32_t)hb;
             const uint32_t hcost = wave_min_u32(hc);
             const int32_t i = (int32_t)wave_min_u32(hc == hcost ? hk : ~0u);
-            if ((int32_t)hcost != hown || hcost >= (uint32_t)DINF || i <= s1 || i > t) { status = 2; break; }
+            if ((int32_t)hcost != hown || hcost >= (uint32_t)DINF || i <= s1 || i > t) { status = 2; continue; }
             emit(RK_FWD_SAVE, s, o);
             for (int32_t k = lane; k < i - s - 1; k += 64) {
                 const int64_t at = n + 2 * (int64_t)k;
@@ -1536,19 +1664,21 @@ __global__ __launch_bounds__(64) void k_backtrace(DevChain ch, Tables tb, int32_
             }
             n += 2 * (int64_t)(i - s - 1);
             push(Frame{1, RK_BWD, s, o});
-            push(Frame{0, s1, i - 1, m - xb});
+            push(Frame{0, s1 | (i - 1) << 11, m - xb, -1});
             push(Frame{1, RK_REFWD, s, o});
             push(Frame{1, RK_FREE_X, i, -1});
             have = true;
             s = i;
             m = u - xs[i];
+            own = -1;
         } else if (code >= (uint32_t)L) {
             const int32_t o = (int32_t)code - L;
             emit(RK_FWD_SAVE, s, o);
             push(Frame{1, RK_BWD, s, o});
             have = t > s;
-            m -= xbar[s * K + o];
+            m -= option(s * K + o).x;
             s += 1;
+            own = next;
         } else {
             // forward through blocks s..i-1 keeping nothing, dropping x_{s+1}..x_{i-1} behind
             const int32_t i = (int32_t)code;
@@ -1559,14 +1689,15 @@ __global__ __launch_bounds__(64) void k_backtrace(DevChain ch, Tables tb, int32_
                 if (at + 1 < cap) ops[at + 1] = rk_op{RK_FREE_X, s + 1 + k, -1};
             }
             n += 2 * (int64_t)(i - s - 1);
-            push(Frame{0, s, i - 1, m});
+            push(Frame{0, s | (i - 1) << 11, m, side});
             push(Frame{1, RK_FREE_X, i, -1});
             have = true;
             s = i;
             m -= xs[i];
+            own = next;
         }
     }
-    if (lane == 0) {
+    if (tid == 0) {
         res[0] = n;
         res[1] = nfwd;
         res[2] = status;
@@ -1576,13 +1707,14 @@ __global__ __launch_bounds__(64) void k_backtrace(DevChain ch, Tables tb, int32_
 hipError_t launch_backtrace(const DevChain &ch, const Tables &tb, int32_t m_top, rk_op *ops,
                             int64_t cap, int64_t *res, hipStream_t stream)
 {
-    const bool xbar_lds = (int64_t)ch.L * ch.K <= BT_XBAR_LDS_MAX;
-    const size_t lds = sizeof(Frame) * (size_t)bt_stack_cap(ch) + sizeof(int32_t) * (size_t)(ch.L + 1) +
-                       (xbar_lds ? sizeof(int32_t) * (size_t)ch.L * ch.K : 0);
-    if (xbar_lds)
-        hipLaunchKernelGGL(k_backtrace<true>, dim3(1), dim3(64), lds, stream, ch, tb, m_top, ops, cap, res);
-    else
-        hipLaunchKernelGGL(k_backtrace<false>, dim3(1), dim3(64), lds, stream, ch, tb, m_top, ops, cap, res);
+    const int32_t steps = bt_steps(ch);
+    size_t lds = sizeof(Frame) * (size_t)bt_stack_cap(ch) + 3 * sizeof(int32_t) * (size_t)(ch.L + 1) +
+                 (steps > 1 ? sizeof(int32_t) * BT_WINDOW : 0);
+    const size_t opts = sizeof(i32x4) * (size_t)ch.L * ch.K;
+    const bool in_lds = lds + opts <= BT_LDS;
+    if (in_lds) lds += opts;
+    hipLaunchKernelGGL(in_lds ? k_backtrace<true> : k_backtrace<false>, dim3(1), dim3(BT_THREADS), lds, stream, ch, tb,
+                       m_top, steps, ops, cap, res);
     return hipGetLastError();
 }
 

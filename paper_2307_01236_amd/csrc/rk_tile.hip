@@ -120,7 +120,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
 
     // Per row ls of this wave (lane ls; lane 16: the row below the tile): what the solve
     // reads per row, fetched once.
-    int32_t r_lb, r_msa, r_P, r_need2, r_PT, r_x, r_need1max;
+    int32_t r_lb, r_msa, r_P, r_need2, r_PT, r_x, r_need1max, r_P1;
     {
         const int32_t te = min(t, L - 1), s = min(S0 + min(lane, TB), te);
         const int64_t r = row_of(L, s, te);
@@ -130,6 +130,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         r_need2 = te + 1 < L ? ch.need2[(int64_t)s * L + te + 1] : 0;
         r_PT = !DIAG && T0 + 1 < L ? ch.P[(int64_t)s * L + T0 + 1] : 0;
         r_x = ch.x[min(S0 + lane, L)];
+        r_P1 = ch.P[(int64_t)s * L + min(s + 1, L - 1)];
         r_need1max = ch.need1max[s];
     }
     auto at = [](int32_t v, int32_t l) { return __builtin_amdgcn_readlane(v, l); };
@@ -331,7 +332,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     if constexpr (NW > 0) {
 #pragma unroll
         for (int32_t k = 0; k < NW; ++k)
-            wn[64 * k] = DIAG || k < NH ? DINF : tb.opt[r1 * stride + tb.padl + m];  // the row below the tile
+            wn[64 * k] = DIAG || k < NH ? DINF : tb.opt[r1 * stride + tb.padl + m] & DINF;  // the row below the tile
     }
     int32_t best = DINF;
     for (int32_t ls = top; ls >= -1; --ls) {
@@ -370,11 +371,14 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
             return __any(bad < 0);
         };
         auto finish = [&](bool again) {
-            if (!again) return;
-            settle(get);
-            if (dead)
+            if (again) {
+                settle(get);
+                if (dead)
 #pragma unroll
-                for (int32_t &v : wv) v = v < 0 ? DINF : v;
+                    for (int32_t &v : wv) v = v < 0 ? DINF : v;
+            }
+#pragma unroll
+            for (int32_t &v : wv) v &= DINF;  // (the mark)
         };
         const bool again = wait && get();
         // row s+1's ap and row s+2's os, after the loads they would otherwise hold up
@@ -416,10 +420,13 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         }
         if (!need_os) os[1] = DINF;
         if (ls < 0) break;
+        bool only1;  // no split reaches the value
         if (closed) {
             best = lb;
+            only1 = !rest || at(r_P1, ls) > 0;  // splits cost at least lb + r(F_s^0)
         } else {
-            best = min(b0, as[0] + os[1]);
+            b0 = min(b0, as[0] + os[1]);  // the splits; best: case 1
+            best = DINF;
             // case 1
             const bool all = mb >= at(r_need1max, ls);
             for (int32_t o = 0;;) {
@@ -439,22 +446,28 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
                 if constexpr (NW == 0) finish(wait);
             }
             // splits inside block T: each costs at least lb(s,t) + P(s, T0+1)
-            if constexpr (!DIAG)
-                if (lt > 0 && __any(best > lb + at(r_PT, ls))) {
+            bool left = false;  // splits left out could reach the value
+            if constexpr (!DIAG) {
+                const int32_t bound = lb + at(r_PT, ls);
+                if (lt > 0 && __any(min(best, b0) > bound)) {
                     wait_waves(0, lt, ls);
                     const int32_t *const ac = cells + (ls * TB * 64 + lane);
                     auto piece = [&](auto v0, auto v1) {
                         if (decltype(v0)::value < lt)
 #pragma unroll
                             for (int32_t v = decltype(v0)::value; v < decltype(v1)::value; ++v)
-                                best = min(best, ac[v * 64] + ost[v]);
+                                b0 = min(b0, ac[v * 64] + ost[v]);
                     };
                     piece(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
                     piece(std::integral_constant<int, 8>{}, std::integral_constant<int, TB - 1>{});
+                } else {
+                    left = lt > 0 && best == bound;
                 }
-            best = min(best, DINF);
+            }
+            only1 = best < min(b0, DINF) && !left;
+            best = min(min(best, b0), DINF);
         }
-        st_dev(best, tb.opt + r0 * stride + tb.padl + m);
+        st_dev(only1 ? best | ONLY_CASE1 : best, tb.opt + r0 * stride + tb.padl + m);
         if constexpr (NW > 0) wn[64 * NH] = best;
         a_prev = m >= at(r_need2, ls) ? min(at(r_P, ls) + best, DINF) : DINF;
         if constexpr (DIAG) aps[tri(ls, n_in) * 64 + lane] = a_prev;  // (unused where lt = 15)
