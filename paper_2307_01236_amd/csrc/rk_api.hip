@@ -51,16 +51,17 @@ struct rk_chain {
     hipStream_t g_stream = nullptr;
     bool g_prof = false;
 
-    rk_op *d_ops = nullptr;  // backtrace output
-    int64_t d_ops_cap = 0;
-    int64_t fills = 0;           // solves queued so far
-    int64_t bt_fill = -1;        // the solve whose schedule d_ops holds
-    int64_t bt_res[3] = {0, 0, 0};
-    int64_t *d_res = nullptr;
-    int32_t *host = nullptr;  // pinned: Tables::host
+    rk_op *ops = nullptr;  // backtrace output: pinned
+    int64_t ops_cap = 0;
+    int64_t fills = 0;     // solves queued so far
+    int64_t bt_fill = -1;  // the solve whose schedule ops holds
+    // Results come back through pinned host memory that the kernels write, so that a call waits
+    // once (a blocking copy into pageable memory takes 15-20 us).
+    int32_t *host = nullptr;   // Tables::host
+    int64_t *bt_res = nullptr; // backtrace: steps, first backward, status
     bool tiled = false;       // the last fill ran by tiles (its answer is in host[0])
-    int16_t *d_argrow = nullptr;
-    int32_t d_argrow_cap = 0;
+    int32_t *rowbuf = nullptr;  // a row: its values, then its codes
+    int32_t rowbuf_cap = 0;
 };
 
 // Wait for the last fill queued by the library.  A fill inside the caller's graph runs when
@@ -121,9 +122,14 @@ int geometry(const rk_chain *c, int32_t M, Geometry *g, size_t *bytes)
 
 // First solve on a device (or the first after the pruning switch changed): upload the
 // derived arrays; create the events and streams once.
-int ensure_device(rk_chain *c)
+bool set_up(const rk_chain *c)
 {
-    if (c->d_chain && c->run_prune == c->prune && c->run_version == c->host_version) return RK_OK;
+    return c->d_chain && c->run_prune == c->prune && c->run_version == c->host_version && c->ev_fill0 && c->ev_fill1 &&
+           c->own_stream && c->host;
+}
+
+int upload(rk_chain *c)
+{
     if (c->d_chain) {  // rebuild: the captured launch sequence holds the old arrays
         if (c->queued) HIPCHK(wait_fill(c));
         HIPCHK(hipFree(c->d_chain));
@@ -141,6 +147,7 @@ int ensure_device(rk_chain *c)
     const bool sweep = !c->h.refwd.empty();
     const size_t nx = L + 1, nk = (size_t)L * K, nl = (size_t)L * L, nr = (size_t)rk::n_rows(L);
     const size_t total = 4 * nk + nx + 3 * nk + L + 2 * nl + 2 * nr + (sweep ? nk + nl : 0);
+    std::vector<int32_t> opt4(4 * nk);
     HIPCHK(hipMalloc(&c->d_chain, total * sizeof(int32_t)));
     int32_t *p = static_cast<int32_t *>(c->d_chain);
     size_t off = 0;
@@ -151,7 +158,6 @@ int ensure_device(rk_chain *c)
                    ? dst
                    : nullptr;
     };
-    std::vector<int32_t> opt4(4 * nk, 0);
     int64_t reach = 0;
     for (size_t j = 0; j < nk; ++j) {
         opt4[4 * j] = c->run.xbar[j];
@@ -191,15 +197,24 @@ int ensure_device(rk_chain *c)
     if (!c->ev_fill0) HIPCHK(hipEventCreate(&c->ev_fill0));
     if (!c->ev_fill1) HIPCHK(hipEventCreate(&c->ev_fill1));
     if (!c->own_stream) HIPCHK(hipStreamCreateWithFlags(&c->own_stream, hipStreamNonBlocking));
-    if (!c->d_res && hipMalloc(&c->d_res, 4 * sizeof(int64_t)) != hipSuccess) {
-        c->d_res = nullptr;
-        return RK_E_NOMEM;
-    }
-    if (!c->host && hipHostMalloc(&c->host, 2 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
-        c->host = nullptr;
-        return RK_E_NOMEM;
+    if (!c->host) {
+        if (hipHostMalloc(&c->host, 64, hipHostMallocDefault) != hipSuccess) {
+            c->host = nullptr;
+            return RK_E_NOMEM;
+        }
+        c->bt_res = reinterpret_cast<int64_t *>(c->host + 4);
     }
     return RK_OK;
+}
+
+int ensure_device(rk_chain *c)
+{
+    if (set_up(c)) return RK_OK;
+    try {
+        return upload(c);
+    } catch (...) {
+        return RK_E_NOMEM;
+    }
 }
 
 // an opt entry as the ABI shows it (opt entries carry the ONLY_CASE1 mark)
@@ -332,6 +347,27 @@ int answer(rk_chain *c, int32_t *out)
     return RK_OK;
 }
 
+// Row (s, t) of the last solve, which is complete, into the pinned row buffer, waiting for it (on
+// the chain's own stream: the caller's may be gone by now).
+int read_row(rk_chain *c, int32_t s, int32_t t, bool codes)
+{
+    if (c->rowbuf_cap < c->W) {
+        if (c->rowbuf) HIPCHK(hipHostFree(c->rowbuf));
+        c->rowbuf = nullptr;
+        c->rowbuf_cap = 0;
+        if (hipHostMalloc(&c->rowbuf, (size_t)c->W * 6 + 64, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            c->rowbuf = nullptr;
+            return RK_E_NOMEM;
+        }
+        c->rowbuf_cap = c->W;
+    }
+    HIPCHK(rk::launch_read_row(c->dc, c->tb, s, t, c->rowbuf,
+                               codes ? reinterpret_cast<int16_t *>(c->rowbuf + c->W) : nullptr, c->own_stream));
+    HIPCHK(hipStreamSynchronize(c->own_stream));
+    return RK_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -388,10 +424,9 @@ void rk_chain_destroy(rk_chain *c)
         if (c->queued && c->ev_fill1) (void)wait_fill(c);
         if (c->d_chain) (void)hipFree(c->d_chain);
         if (c->own_ws) (void)hipFree(c->own_ws);
-        if (c->d_ops) (void)hipFree(c->d_ops);
-        if (c->d_res) (void)hipFree(c->d_res);
+        if (c->ops) (void)hipHostFree(c->ops);
         if (c->host) (void)hipHostFree(c->host);
-        if (c->d_argrow) (void)hipFree(c->d_argrow);
+        if (c->rowbuf) (void)hipHostFree(c->rowbuf);
         if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
         if (c->ev_fill0) (void)hipEventDestroy(c->ev_fill0);
         if (c->ev_fill1) (void)hipEventDestroy(c->ev_fill1);
@@ -424,8 +459,7 @@ int rk_solve_async(rk_chain *c, int32_t M, void *d_workspace, size_t ws_bytes, v
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (stream && hipStreamIsCapturing(static_cast<hipStream_t>(stream), &cs) != hipSuccess) return RK_E_DEVICE;
     if (cs != hipStreamCaptureStatusNone) {
-        if (!c->d_chain || c->run_prune != c->prune || c->run_version != c->host_version || !d_workspace ||
-            c->prof.on)
+        if (!set_up(c) || !d_workspace || c->prof.on)
             return RK_E_INVAL;
         if (ws_bytes < need) return RK_E_NOMEM;
         return fill(c, M, g, static_cast<int32_t *>(d_workspace), static_cast<hipStream_t>(stream), true);
@@ -462,8 +496,7 @@ int rk_solve_noalloc(rk_chain *c, int32_t M, void *stream)
     if (rc != RK_OK) return rc;
     if (need > RK_NOALLOC_MAX_BYTES) return RK_E_NOMEM;
     // the derived arrays, events and stream exist from an earlier solve on this device
-    if (!c->d_chain || c->run_prune != c->prune || c->run_version != c->host_version || c->prof.on ||
-        !c->ev_fill0 || !c->ev_fill1)
+    if (!set_up(c) || c->prof.on)
         return RK_E_INVAL;
     DeviceScope ds(c);
     if (!ds.ok) return RK_E_DEVICE;
@@ -503,33 +536,37 @@ int rk_extract_schedule(rk_chain *c, rk_op *ops, int64_t cap, int64_t *n_ops, in
     int rc = answer(c, &ans);
     if (rc != RK_OK) return rc;
     if (ans == RK_INF) return RK_E_INFEASIBLE;
-    // At most L forwards per block (one saving) and one backward, one forget per no-save forward.
-    // At most L forwards per block (one saving, one re-forward with the saving sweep) and one
-    // backward, one forget per no-save forward.
-    const int64_t max_ops = 3 * (int64_t)c->h.L * c->h.L + 16;
-    if (c->d_ops_cap < max_ops) {
-        if (c->d_ops) HIPCHK(hipFree(c->d_ops));
-        c->d_ops = nullptr;
-        c->d_ops_cap = 0;
-        c->bt_fill = -1;
-        if (hipMalloc(&c->d_ops, max_ops * sizeof(rk_op)) != hipSuccess) return RK_E_NOMEM;
-        c->d_ops_cap = max_ops;
-    }
-    // the schedule of this solve is computed once (the two-call protocol asks twice)
-    int64_t *const res = c->bt_res;
+    // The schedule of this solve is computed once (the two-call protocol asks twice).  Its length
+    // is known only afterwards: 2 to 7 steps a block are usual, up to 3 L^2 possible; one that
+    // does not fit the buffer is computed again into one that it fits.
+    const int64_t *const res = c->bt_res;
     if (c->bt_fill != c->fills) {
         c->bt_fill = -1;
-        HIPCHK(rk::launch_backtrace(c->dc, c->tb, c->M - c->h.x[0], c->d_ops, c->d_ops_cap, c->d_res,
-                                    c->stream));
-        HIPCHK(hipMemcpyAsync(res, c->d_res, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
+        int64_t want = std::max<int64_t>(c->ops_cap, 8 * (int64_t)c->h.L + 64);
+        for (int32_t turn = 0; turn < 2; ++turn) {
+            if (c->ops_cap < want) {
+                if (c->ops) HIPCHK(hipHostFree(c->ops));
+                c->ops = nullptr;
+                c->ops_cap = 0;
+                if (hipHostMalloc(&c->ops, want * sizeof(rk_op), hipHostMallocDefault) != hipSuccess) {
+                    (void)hipGetLastError();
+                    c->ops = nullptr;
+                    return RK_E_NOMEM;
+                }
+                c->ops_cap = want;
+            }
+            HIPCHK(rk::launch_backtrace(c->dc, c->tb, c->M - c->h.x[0], c->ops, c->ops_cap, c->bt_res, c->own_stream));
+            HIPCHK(hipStreamSynchronize(c->own_stream));
+            if (res[2] != 0 || res[0] <= c->ops_cap) break;
+            want = res[0];
+        }
+        if (res[2] != 0 || res[0] > c->ops_cap) return RK_E_INTERNAL;
         c->bt_fill = c->fills;
     }
-    if (res[2] != 0 || res[0] > c->d_ops_cap) return RK_E_INTERNAL;
     *n_ops = res[0];
     if (n_fwd) *n_fwd = res[1];
     if (!ops || cap < res[0]) return RK_E_BUFSZ;
-    HIPCHK(hipMemcpy(ops, c->d_ops, res[0] * sizeof(rk_op), hipMemcpyDeviceToHost));
+    std::copy(c->ops, c->ops + res[0], ops);
     for (int64_t k = 0; k < res[0]; ++k)  // option slots back to the caller's option indices
         if (ops[k].kind == RK_FWD_SAVE || ops[k].kind == RK_BWD || ops[k].kind == RK_REFWD)
             ops[k].option = c->run.opt[(size_t)ops[k].block * c->run.k_run + ops[k].option];
@@ -544,29 +581,16 @@ int rk_read_row(rk_chain *c, int32_t s, int32_t t, int32_t *opt_row, int16_t *ar
     if (!ds.ok) return RK_E_DEVICE;
     HIPCHK(wait_fill(c));
     if (c->tiled && c->host[1]) return RK_E_INTERNAL;
-    const int64_t base = rk::row_of(c->h.L, s, t) * c->tb.stride + c->tb.padl;
-    if (opt_row) {
-        HIPCHK(hipMemcpy(opt_row, c->tb.opt + base, (size_t)c->W * sizeof(int32_t), hipMemcpyDeviceToHost));
-        for (int32_t m = 0; m < c->W; ++m) opt_row[m] = to_abi(opt_row[m]);
-    }
+    int rc = read_row(c, s, t, arg_row != nullptr);
+    if (rc != RK_OK) return rc;
+    if (opt_row) std::copy(c->rowbuf, c->rowbuf + c->W, opt_row);
     if (arg_row) {
-        if (c->d_argrow_cap < c->W) {
-            if (c->d_argrow) HIPCHK(hipFree(c->d_argrow));
-            c->d_argrow = nullptr;
-            c->d_argrow_cap = 0;
-            if (hipMalloc(&c->d_argrow, (size_t)c->W * sizeof(int16_t)) != hipSuccess) return RK_E_NOMEM;
-            c->d_argrow_cap = c->W;
+        const int16_t *const code = reinterpret_cast<const int16_t *>(c->rowbuf + c->W);
+        const int32_t *const slot = c->run.opt.data() + (size_t)s * c->run.k_run;
+        for (int32_t m = 0; m < c->W; ++m) {  // option slots back to the caller's option indices
+            const int32_t v = code[m], o = v - c->h.L, o3 = o - c->run.k_run;
+            arg_row[m] = (int16_t)(o < 0 ? v : o3 < 0 ? c->h.L + slot[o] : c->h.L + c->h.K + slot[o3]);  // o3: case 3
         }
-        HIPCHK(rk::launch_arg_row(c->dc, c->tb, s, t, c->d_argrow, c->stream));
-        HIPCHK(hipMemcpyAsync(arg_row, c->d_argrow, (size_t)c->W * sizeof(int16_t),
-                              hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        for (int32_t m = 0; m < c->W; ++m)  // option slots back to the caller's option indices
-            if (arg_row[m] >= c->h.L + c->run.k_run)  // case 3 (the saving sweep)
-                arg_row[m] = (int16_t)(c->h.L + c->h.K +
-                                       c->run.opt[(size_t)s * c->run.k_run + (arg_row[m] - c->h.L - c->run.k_run)]);
-            else if (arg_row[m] >= c->h.L)
-                arg_row[m] = (int16_t)(c->h.L + c->run.opt[(size_t)s * c->run.k_run + (arg_row[m] - c->h.L)]);
     }
     return RK_OK;
 }
@@ -584,9 +608,9 @@ int rk_tradeoff_curve(rk_chain *c, int32_t *times, int64_t n)
     const int64_t x0 = c->h.x[0], lead = std::min<int64_t>(n, x0);
     for (int64_t b = 0; b < lead; ++b) times[b] = RK_INF;
     if (n > x0) {
-        const int64_t base = rk::row_of(c->h.L, 0, c->h.L - 1) * c->tb.stride + c->tb.padl;
-        HIPCHK(hipMemcpy(times + x0, c->tb.opt + base, (size_t)(n - x0) * sizeof(int32_t), hipMemcpyDeviceToHost));
-        for (int64_t b = x0; b < n; ++b) times[b] = to_abi(times[b]);
+        int rc = read_row(c, 0, c->h.L - 1, false);
+        if (rc != RK_OK) return rc;
+        std::copy(c->rowbuf, c->rowbuf + (n - x0), times + x0);
     }
     return RK_OK;
 }

@@ -1314,30 +1314,26 @@ __device__ inline int32_t opt_at(const Tables &tb, int32_t L, int32_t s, int32_t
     return tb.opt[row_of(L, s, t) * tb.stride + tb.padl + m] & DINF;  // (without ONLY_CASE1)
 }
 
+// (Loads at clamped columns, so that a candidate's do not wait for its validity.)
 __device__ inline uint64_t split_key(const DevChain &ch, const Tables &tb, int32_t s, int32_t t,
                                      int32_t m, int32_t i)
 {
     const int32_t L = ch.L;
-    if (m < ch.need2[s * L + i]) return ~0ull;
     const int32_t a = opt_at(tb, L, s, i - 1, m);
-    const int32_t q = opt_at(tb, L, i, t, m - ch.x[i]);
-    if (a >= DINF || q >= DINF) return ~0ull;
-    const int64_t v = (int64_t)ch.P[s * L + i] + a + q;
-    if (v >= DINF) return ~0ull;
-    return ((uint64_t)v << 32) | (uint32_t)i;
+    const int32_t q = opt_at(tb, L, i, t, max(m - ch.x[i], 0));
+    const uint32_t v = (uint32_t)ch.P[s * L + i] + (uint32_t)a + (uint32_t)q;
+    const bool ok = m >= ch.need2[s * L + i] && a < DINF && q < DINF && v < (uint32_t)DINF;
+    return ok ? ((uint64_t)v << 32) | (uint32_t)i : ~0ull;
 }
 
 __device__ inline uint64_t option_key(const DevChain &ch, const Tables &tb, int32_t s, int32_t t,
                                       int32_t m, int32_t o)
 {
     const int32_t L = ch.L, K = ch.K;
-    if (m < ch.need1[s * K + o]) return ~0ull;
-    int32_t rest = 0;
-    if (t > s) rest = opt_at(tb, L, s + 1, t, m - ch.xbar[s * K + o]);
-    if (rest >= DINF) return ~0ull;
-    const int64_t v = (int64_t)ch.c1[s * K + o] + rest;
-    if (v >= DINF) return ~0ull;
-    return ((uint64_t)v << 32) | (uint32_t)(L + o);
+    const int32_t r = opt_at(tb, L, min(s + 1, t), t, max(m - ch.xbar[s * K + o], 0)), rest = t > s ? r : 0;
+    const uint32_t v = (uint32_t)ch.c1[s * K + o] + (uint32_t)rest;
+    const bool ok = m >= ch.need1[s * K + o] && rest < DINF && v < (uint32_t)DINF;
+    return ok ? ((uint64_t)v << 32) | (uint32_t)(L + o) : ~0ull;
 }
 
 // Case 3 (the saving sweep) with option slot o: code L + K + o.
@@ -1354,24 +1350,45 @@ __device__ inline uint64_t sweep_key(const DevChain &ch, const Tables &tb, int32
     return ((uint64_t)v << 32) | (uint32_t)(L + K + o);
 }
 
-// One row of choice codes: thread m scans the candidates in code order.
-__global__ __launch_bounds__(256) void k_arg_row(DevChain ch, Tables tb, int32_t s, int32_t t,
-                                                 int16_t *__restrict__ out)
+// One row, values and (codes non-null) choice codes, written to host memory: a workgroup
+// covers 64 budgets, its waves share the candidates (every wave its own in code order, so a
+// strict comparison keeps the smallest code).  Bound by the round trips of the candidates' loads:
+// one thread per budget scanning them all took 35 us a row at 128 blocks x 2001 budgets, this
+// takes 5.8 us.
+constexpr int32_t AR_WAVES = 16;
+__global__ __launch_bounds__(64 * AR_WAVES) void k_read_row(DevChain ch, Tables tb, int32_t s, int32_t t,
+                                                            int32_t *__restrict__ values, int16_t *__restrict__ codes)
 {
-    const int32_t m = blockIdx.x * 256 + threadIdx.x;
-    if (m >= tb.W) return;
-    uint64_t best = ~0ull;
-    for (int32_t i = s + 1; i <= t; ++i) best = min(best, split_key(ch, tb, s, t, m, i));
-    for (int32_t o = 0; o < ch.K; ++o) best = min(best, option_key(ch, tb, s, t, m, o));
-    if (ch.c3)
-        for (int32_t o = 0; o < ch.K; ++o) best = min(best, sweep_key(ch, tb, s, t, m, o));
-    out[m] = best == ~0ull ? (int16_t)-1 : (int16_t)(best & 0xffffu);
+    __shared__ uint64_t part[AR_WAVES][64];
+    const int32_t lane = (int32_t)(threadIdx.x & 63), m = (int32_t)blockIdx.x * 64 + lane, mc = min(m, tb.W - 1);
+    const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
+    if (codes) {
+        uint64_t best = ~0ull;
+        auto take = [&](uint64_t key) { best = key < best ? key : best; };
+#pragma unroll 4
+        for (int32_t i = s + 1 + wave; i <= t; i += AR_WAVES) take(split_key(ch, tb, s, t, mc, i));
+        for (int32_t o = wave; o < ch.K; o += AR_WAVES) {
+            take(option_key(ch, tb, s, t, mc, o));
+            if (ch.c3) take(sweep_key(ch, tb, s, t, mc, o));
+        }
+        part[wave][lane] = best;
+        __syncthreads();
+        if (wave == 0 && m < tb.W) {
+            for (int32_t w = 1; w < AR_WAVES; ++w) take(part[w][lane]);
+            codes[m] = best == ~0ull ? (int16_t)-1 : (int16_t)(best & 0xffffu);
+        }
+    }
+    if (wave == 0 && m < tb.W) {
+        const int32_t v = opt_at(tb, ch.L, s, t, m);
+        values[m] = v >= DINF ? RK_INF : v;
+    }
 }
 
-hipError_t launch_arg_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, int16_t *out,
-                          hipStream_t stream)
+hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, int32_t *values, int16_t *codes,
+                           hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_arg_row, dim3((tb.W + 255) / 256), dim3(256), 0, stream, ch, tb, s, t, out);
+    hipLaunchKernelGGL(k_read_row, dim3((tb.W + 63) / 64), dim3(codes ? 64 * AR_WAVES : 64), 0, stream, ch, tb, s, t,
+                       values, codes);
     return hipGetLastError();
 }
 
