@@ -131,9 +131,9 @@ int rk_solve(rk_chain *c, int32_t M, int32_t *opt_out);
  * Same fill, asynchronous, in caller memory: d_workspace is device memory of
  * at least rk_workspace_bytes(c, M) bytes (for instance a torch tensor) and
  * stream a hipStream_t (NULL: a stream the chain owns).  Returns once the work
- * is queued.  The fill's kernel sequence is captured into a HIP graph on first
- * use and replayed while M, the workspace, the stream and the profiling switch
- * stay the same.  The workspace must stay allocated and untouched until the
+ * is queued.  With the saving sweep the fill's kernel sequence is captured into a HIP graph on
+ * first use and replayed while M, the workspace, the stream and the profiling switch
+ * stay the same; without it the fill's few launches go straight to the stream.  The workspace must stay allocated and untouched until the
  * chain is destroyed or solved again; the chain reads results from it.  Call
  * rk_result to wait and read the answer.
  *

@@ -146,30 +146,33 @@ int upload(rk_chain *c)
     const int32_t L = c->h.L, K = c->run.k_run;
     const bool sweep = !c->h.refwd.empty();
     const size_t nx = L + 1, nk = (size_t)L * K, nl = (size_t)L * L, nr = (size_t)rk::n_rows(L);
-    const size_t total = 4 * nk + nx + 3 * nk + L + 2 * nl + 2 * nr + (sweep ? nk + nl : 0);
-    std::vector<int32_t> opt4(4 * nk);
+    const size_t K4 = ((size_t)K + 3) / 4 * 4, nk4 = L * K4;
+    const size_t total = 4 * nk4 + nx + 3 * nk + L + 2 * nl + 2 * nr + (sweep ? nk + nl : 0);
+    std::vector<int32_t> all(total), opt4(4 * nk4);  // one copy for all arrays (each costs 10 us)
     HIPCHK(hipMalloc(&c->d_chain, total * sizeof(int32_t)));
     int32_t *p = static_cast<int32_t *>(c->d_chain);
     size_t off = 0;
     auto put = [&](const std::vector<int32_t> &v) -> const int32_t * {
-        int32_t *dst = p + off;
+        std::copy(v.begin(), v.end(), all.begin() + off);
         off += v.size();
-        return hipMemcpy(dst, v.data(), v.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess
-                   ? dst
-                   : nullptr;
+        return p + off - v.size();
     };
     int64_t reach = 0;
-    for (size_t j = 0; j < nk; ++j) {
-        opt4[4 * j] = c->run.xbar[j];
-        opt4[4 * j + 1] = c->run.c1[j];
-        opt4[4 * j + 2] = c->run.need1[j];
-        opt4[4 * j + 3] = (int32_t)std::min<int64_t>(4 * (int64_t)c->run.xbar[j], INT32_MAX);
-        reach = std::max<int64_t>(reach, c->run.xbar[j]);
+    for (size_t j = 0; j < nk4; ++j) {
+        const size_t s = j / K4, o = j % K4, q = s * K + o;
+        const bool real = o < (size_t)K;
+        const int32_t xbar = real ? c->run.xbar[q] : c->h.x[s + 1];
+        opt4[4 * j] = xbar;
+        opt4[4 * j + 1] = real ? c->run.c1[q] : DINF;
+        opt4[4 * j + 2] = real ? c->run.need1[q] : xbar;
+        opt4[4 * j + 3] = (int32_t)std::min<int64_t>(4 * (int64_t)xbar, INT32_MAX);
+        reach = std::max<int64_t>(reach, xbar);
     }
     for (int32_t v : c->h.x) reach = std::max<int64_t>(reach, v);
     c->dc.reach = (int32_t)std::min<int64_t>(reach, 1 << 30);
     c->dc.L = L;
     c->dc.K = K;
+    c->dc.K4 = (int32_t)K4;
     c->dc.opt4 = put(opt4);  // first: 16-byte aligned
     c->dc.x = put(c->h.x);
     c->dc.xbar = put(c->run.xbar);
@@ -187,8 +190,8 @@ int upload(rk_chain *c)
     int64_t xbar_max = 0;
     for (int32_t v : c->run.xbar) xbar_max = std::max<int64_t>(xbar_max, v);
     c->dc.xbar_halo = xbar_max > rk::HMAX ? rk::HMAX + 1 : rk::round64(xbar_max);
-    if (!c->dc.x || !c->dc.xbar || !c->dc.c1 || !c->dc.need1 || !c->dc.need1max || !c->dc.P ||
-        !c->dc.need2 || !c->dc.lb || !c->dc.msa || !c->dc.opt4 || (sweep && (!c->dc.c3 || !c->dc.need3))) {  // leave no half-uploaded arrays behind: the next solve uploads again
+    // leave no half-uploaded arrays behind: the next solve uploads again
+    if (off > total || hipMemcpy(p, all.data(), off * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(c->d_chain);
         c->d_chain = nullptr;
         return RK_E_DEVICE;
@@ -288,7 +291,9 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
     if (!c->in_caller_graph) HIPCHK(hipEventRecord(c->ev_fill0, stream));
     const bool replay = c->gexec && c->g_M == M && c->g_tables == tables && c->g_stream == stream &&
                         c->g_prof == c->prof.on;
-    if (direct) {
+    // The tiled fill's few long kernels are launched one by one: the host stays ahead of them, and
+    // a graph of them would cost more to build than it saves.
+    if (direct || c->tiled) {
         c->prof.reset(stream);
         HIPCHK(launch());
     } else if (replay) {

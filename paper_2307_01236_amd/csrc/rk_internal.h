@@ -97,7 +97,10 @@ struct DevChain {
     const int32_t *need3;
     const int32_t *h_msaH;  // [L(L+1)/2], host memory: from msaH(s,t) on, H(s,t) = lb(s,t) + P[s][s+1]
     const int32_t *msa;    // [L(L+1)/2]  h_msa on the device
-    const int32_t *opt4;   // [L*K][4]  xbar, c1, need1, 4 xbar of an option together
+    // [L*K4][4], K4 = K rounded up to 4: xbar, c1, need1, 4 xbar of an option together (the padding
+    // like that of the run slots)
+    const int32_t *opt4;
+    int32_t K4;
     int32_t reach;         // how far left of a column its cell reads: max of xbar and x
     int32_t xbar_halo;     // round64(max xbar): how far left case 1 reads from column m
 };

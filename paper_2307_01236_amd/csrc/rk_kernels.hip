@@ -1447,14 +1447,14 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
     extern __shared__ __align__(16) int32_t sh[];
     __shared__ i32x4 found[BT_WAVES];  // per wave: cost, code, entry of the next cell, entry of the left sub-span
     __shared__ int32_t order[6];       // what the first wave wants: mode, s, t, m, steps, the cell's entry
-    const int32_t L = ch.L, K = ch.K, tid = (int32_t)threadIdx.x, lane = tid & 63;
+    const int32_t L = ch.L, K = ch.K, K4 = ch.K4, tid = (int32_t)threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t stack_cap = bt_stack_cap(ch);
     const bool sweep = ch.c3 != nullptr;
     Frame *const stk = reinterpret_cast<Frame *>(sh);
     // options of every block (xbar, r(F)+r(B), need1): in LDS where they fit
     i32x4 *const lo = reinterpret_cast<i32x4 *>(sh + 4 * stack_cap);
-    int32_t *const win = sh + 4 * stack_cap + (OPTS_LDS ? 4 * L * K : 0);
+    int32_t *const win = sh + 4 * stack_cap + (OPTS_LDS ? 4 * L * K4 : 0);
     int32_t *const xs = win + (steps > 1 ? BT_WINDOW : 0);  // x_0..x_L
     int32_t *const fs = xs + L + 1;  // F(i) = P[0][i], the no-save forwards before block i
     int32_t *const lbs = fs + L + 1; // lb(0, i-1): lb(s, t) = lbs[t+1] - lbs[s]
@@ -1465,7 +1465,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
     }
     if constexpr (OPTS_LDS)
 #pragma unroll 4
-        for (int32_t j = tid; j < L * K; j += BT_THREADS) lo[j] = ((const i32x4 *)ch.opt4)[j];
+        for (int32_t j = tid; j < L * K4; j += BT_THREADS) lo[j] = ((const i32x4 *)ch.opt4)[j];
     const int64_t stride = tb.stride;
     const int32_t padl = tb.padl, X = ch.reach;
     auto option = [&](int32_t j) -> i32x4 {
@@ -1574,7 +1574,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
                 const int32_t *const hbelow = sweep ? tb.hopt + row_of(L, min(cs + 1, ct), ct) * stride + padl : below;
                 const int32_t x1 = xs[min(cs + 1, L)];
                 for (int32_t o = tid - 64 * BT_SPLIT_WAVES; o < K; o += BT_THREADS - 64 * BT_SPLIT_WAVES) {
-                    const i32x4 q = option(cs * K + o);
+                    const i32x4 q = option(cs * K4 + o);
                     const int32_t v = below[(uint32_t)max(cm - q.x, 0)];
                     // case 3: c3 + H(s+1, t, m - mem), mem = xbar - x_{s+1}
                     const int32_t h = sweep ? hbelow[(uint32_t)min(max(cm - (q.x - x1), 0), tb.W - 1)] : DINF;
@@ -1597,7 +1597,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
             const int32_t s0 = s;
             int32_t chosen = 0, j = 0;
             const int32_t *row = win + (64 * pieces - 1 - m);  // row s + 1, at column 0
-            i32x4 p = option(s * K + min(lane, K - 1));
+            i32x4 p = option(s * K4 + min(lane, K - 1));
             bool more = true;  // the cell is one to walk from
             auto step = [&](uint64_t hit, int32_t o0, int32_t r) {  // the chosen option's, and on to row s + 1
                 const int32_t l = (int32_t)__builtin_ctzll(hit);
@@ -1611,7 +1611,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
             if (steps > 1 && K <= 64) {
                 const int32_t lc = min(lane, K - 1);
                 while (more && s < t) {
-                    const i32x4 p1 = option((s + 1) * K + lc);  // the next row's options, in flight meanwhile
+                    const i32x4 p1 = option((s + 1) * K4 + lc);  // the next row's options, in flight meanwhile
                     const int32_t r = row[m - p.x];  // in the window whether the option fits or not: xbar <= reach
                     const uint64_t hit = __ballot(m >= p.z && p.y + (r & DINF) == (own & DINF));
                     if (!hit) { status = 2; more = false; break; }
@@ -1625,7 +1625,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
                 int32_t o0 = 0, r = 0;
                 uint64_t hit = 0;
                 for (; o0 < K && !hit; o0 += 64) {
-                    p = option(s * K + min(o0 + lane, K - 1));
+                    p = option(s * K4 + min(o0 + lane, K - 1));
                     const int32_t c = m - p.x;
                     if (!last) r = steps > 1 ? row[c] : entry(s + 1, t, max(c, 0));
                     hit = __ballot(m >= p.z && p.y + (r & DINF) == (own & DINF));
@@ -1658,7 +1658,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
             // (s+1, t, u = m - mem); then i..t, x_i dropped, x_{s+1} made again from the kept
             // data, s+1..i-1, and B_s^o
             const int32_t o = (int32_t)code - L - K, s1 = s + 1;
-            const int32_t xb = option(s * K + o).x;
+            const int32_t xb = option(s * K4 + o).x;
             const int32_t u = m - (xb - xs[s1]);
             const int32_t hown = tb.hopt[row_of(L, s1, t) * stride + padl + u];
             const int32_t *const aq_s = tb.aq + row_of(L, s1, s1) * stride + padl + u - min(xs[s1], padl);
@@ -1693,7 +1693,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
             emit(RK_FWD_SAVE, s, o);
             push(Frame{1, RK_BWD, s, o});
             have = t > s;
-            m -= option(s * K + o).x;
+            m -= option(s * K4 + o).x;
             s += 1;
             own = next;
         } else {
@@ -1727,7 +1727,7 @@ hipError_t launch_backtrace(const DevChain &ch, const Tables &tb, int32_t m_top,
     const int32_t steps = bt_steps(ch);
     size_t lds = sizeof(Frame) * (size_t)bt_stack_cap(ch) + 3 * sizeof(int32_t) * (size_t)(ch.L + 1) +
                  (steps > 1 ? sizeof(int32_t) * BT_WINDOW : 0);
-    const size_t opts = sizeof(i32x4) * (size_t)ch.L * ch.K;
+    const size_t opts = sizeof(i32x4) * (size_t)ch.L * ch.K4;
     const bool in_lds = lds + opts <= BT_LDS;
     if (in_lds) lds += opts;
     hipLaunchKernelGGL(in_lds ? k_backtrace<true> : k_backtrace<false>, dim3(1), dim3(BT_THREADS), lds, stream, ch, tb,

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     static_assert(TCI == 4 && TB == 16, "a wave stages four rows of one split");
     static_assert(2 * TCI * 2 * TB <= TB * TB, "two staging buffers fit the tile");
 
-    const int32_t L = ch.L, K = ch.K;
+    const int32_t L = ch.L, K4 = ch.K4;
     int32_t chunk, sb;
     chunk_tile(blockIdx.x, (uint32_t)((L + TB - 1) / TB - level), &chunk, &sb);
     if (chunk >= n_chunks) return;
@@ -306,12 +306,11 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
-    // a finished row of ap (0) or os (1), and its last value in the summaries
-    const int32_t grp = chunk / max(cpe, 1);
-    const bool grp_end = cpe > 0 && lane == 63 && (chunk + 1 == n_chunks || (chunk + 1) % max(cpe, 1) == 0);
-    auto put = [&](int32_t v, int32_t *tab, int32_t which, int64_t r) {
-        __builtin_nontemporal_store(v, tab + r * stride + tb.padl + m);
-        if (grp_end) *sum_at(tb, 2 * grp + which, (int32_t)r) = v;
+    // the last values of the rows of ap and os (lane: ls), for the summaries
+    int32_t end_a = 0, end_os = 0;
+    auto last = [&](int32_t v, int32_t ls, int32_t &ends) {
+        const int32_t end = __builtin_amdgcn_readlane(v, 63);
+        ends = lane == ls ? end : ends;
     };
 
     // Rows from the last to the first, and one more turn (ls = -1) that only completes the
@@ -323,7 +322,10 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     for (int32_t u = 0; u < TB; ++u) os[u] = DINF;
     int32_t a_prev = 0, os_prev = 0;  // ap and os values not stored yet
     const int32_t top = DIAG ? lt : TB - 1;
-    int64_t r0 = row_of(L, S0 + top, t), r1 = r0 + (L - 1 - (S0 + top)), r2 = r1;  // rows (s, t), (s+1, t), (s+2, t)
+    // entries of rows (s, t), (s+1, t), (s+2, t) at this wave's first column; row (s-1, t) lies
+    // L - s rows before (s, t)
+    const int32_t stride32 = (int32_t)stride;
+    int64_t e0 = row_of(L, S0 + top, t) * stride + tb.padl + mb, e1 = e0 + (int64_t)(L - 1 - (S0 + top)) * stride32, e2 = e1;
     // the window of case 1, columns m - 64 NH + 64 k of row (s+1, t); piece NH is this wave's own
     constexpr int32_t NH = NW - 1;
     int32_t *const wn = win + (NW ? lt * NW * 64 + lane : 0);
@@ -332,7 +334,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     if constexpr (NW > 0) {
 #pragma unroll
         for (int32_t k = 0; k < NW; ++k)
-            wn[64 * k] = DIAG || k < NH ? DINF : tb.opt[r1 * stride + tb.padl + m] & DINF;  // the row below the tile
+            wn[64 * k] = DIAG || k < NH ? DINF : tb.opt[e1 + lane] & DINF;  // the row below the tile
     }
     int32_t best = DINF;
     for (int32_t ls = top; ls >= -1; --ls) {
@@ -345,11 +347,11 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         // all columns of row (s+1, t) that this workgroup reads are past its msa (or there is none)
         const bool flat = !rest || mb - reach >= at(r_msa, ls + 1);
         const int32_t fv = rest ? at(r_lb, ls + 1) : 0;
-        const int32_t *const row1 = tb.opt + r1 * stride + tb.padl;
-        const opt_ptr op = (opt_ptr)(uint64_t)ch.opt4 + (int64_t)max(s, 0) * K;
+        const int32_t *const row1 = tb.opt + e1 + lane;  // at column m
+        const opt_ptr op = (opt_ptr)(uint64_t)ch.opt4 + max(s, 0) * K4;
         i32x4 o4[TOPT];
 #pragma unroll
-        for (int32_t j = 0; j < TOPT; ++j) o4[j] = op[min(j, K - 1)];  // xbar, r(F)+r(B), need1, 4 xbar
+        for (int32_t j = 0; j < TOPT; ++j) o4[j] = op[j];  // xbar, r(F)+r(B), need1, 4 xbar
 
         // the loads of row (s+1, t): the window's pieces of other workgroups; without a window
         // the right operand's word and the first options'
@@ -361,12 +363,16 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
             if constexpr (NW > 0) {
 #pragma unroll
                 for (int32_t k = 0; k < NH; ++k)
-                    if (k >= k0) bad |= wv[k] = ld_dev(row1 + (m - 64 * (NH - k)));
+                    if (k >= k0) bad |= wv[k] = ld_dev(row1 - 64 * (NH - k));
             } else {
-                auto word = [&](int32_t c, bool want) { return want && c >= 0 ? ld_dev(row1 + c) : DINF; };
-                bad |= wv[TOPT] = word(m - x1, need_os);
+                // (a scalar base and a 32-bit column)
+                const int32_t *const row1c = tb.opt + (e1 - mb);
+                auto word = [&](int32_t back, bool want) {
+                    return want && m >= back ? ld_dev(row1c + (uint32_t)(m - back)) : DINF;
+                };
+                bad |= wv[TOPT] = word(x1, need_os);
 #pragma unroll
-                for (int32_t j = 0; j < TOPT; ++j) bad |= wv[j] = word(m - o4[j].x, !closed && m >= o4[j].z);
+                for (int32_t j = 0; j < TOPT; ++j) bad |= wv[j] = word(o4[j].x, !closed && m >= o4[j].z);
             }
             return __any(bad < 0);
         };
@@ -382,8 +388,8 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         };
         const bool again = wait && get();
         // row s+1's ap and row s+2's os, after the loads they would otherwise hold up
-        if (need_os) put(a_prev, tb.ap, 0, r1);
-        if (n_in > 1) put(os_prev, tb.os, 1, r2);
+        if (need_os) __builtin_nontemporal_store(a_prev, tb.ap + e1 + lane);
+        if (n_in > 1) __builtin_nontemporal_store(os_prev, tb.os + e2 + lane);
 
         const int32_t *const as = aps + (tri(lsc, 0) * 64 + lane);
         int32_t b0 = DINF;
@@ -418,6 +424,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         } else {
             os[1] = os_prev = flat ? fv : wv[TOPT];
         }
+        last(os_prev, ls + 1, end_os);
         if (!need_os) os[1] = DINF;
         if (ls < 0) break;
         bool only1;  // no split reaches the value
@@ -440,9 +447,9 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
                     for (int32_t j = 0; j < TOPT; ++j) v[j] = m >= o4[j].z ? v[j] : DINF;
 #pragma unroll
                 for (int32_t j = 0; j < TOPT; j += 2) best = min(min(best, v[j]), v[j + 1]);
-                if ((o += TOPT) >= K) break;
+                if ((o += TOPT) >= K4) break;
 #pragma unroll
-                for (int32_t j = 0; j < TOPT; ++j) o4[j] = op[min(o + j, K - 1)];
+                for (int32_t j = 0; j < TOPT; ++j) o4[j] = op[o + j];
                 if constexpr (NW == 0) finish(wait);
             }
             // splits inside block T: each costs at least lb(s,t) + P(s, T0+1)
@@ -467,18 +474,24 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
             only1 = best < min(b0, DINF) && !left;
             best = min(min(best, b0), DINF);
         }
-        st_dev(only1 ? best | ONLY_CASE1 : best, tb.opt + r0 * stride + tb.padl + m);
+        st_dev(only1 ? best | ONLY_CASE1 : best, tb.opt + e0 + lane);
         if constexpr (NW > 0) wn[64 * NH] = best;
         a_prev = m >= at(r_need2, ls) ? min(at(r_P, ls) + best, DINF) : DINF;
+        last(a_prev, ls, end_a);
         if constexpr (DIAG) aps[tri(ls, n_in) * 64 + lane] = a_prev;  // (unused where lt = 15)
         else cells[(ls * TB + lt) * 64 + lane] = a_prev;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         if (lane == 0) __hip_atomic_store(&prog[lt], TB - ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        r2 = r1;
-        r1 = r0;
-        r0 -= L - s;  // (s - 1, t)
+        e2 = e1;
+        e1 = e0;
+        e0 -= (int64_t)(L - s) * stride32;
     }
-    put(os_prev, tb.os, 1, r1);  // row S0
+    __builtin_nontemporal_store(os_prev, tb.os + e1 + lane);  // row S0
+    if (cpe > 0 && (chunk + 1 == n_chunks || (chunk + 1) % cpe == 0) && lane <= top) {
+        const int32_t r = (int32_t)row_of(L, S0 + lane, t), e = 2 * (chunk / cpe);
+        *sum_at(tb, e, r) = end_a;
+        *sum_at(tb, e + 1, r) = end_os;
+    }
     if (S0 == 0 && t == L - 1 && m == m_ans) __hip_atomic_store(tb.host, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
