@@ -26,10 +26,13 @@
 // 1.08 -> 0.46 ms, 256 x 4001 x 8 3.51 -> 2.13 ms, 384 x 6001 x 16 8.2 -> 6.4 ms, 1000 x 601 x 4
 // 24.7 -> 17.3 ms, 61 x 25002 x 4 1.05 -> 0.56 ms.
 //
-// Waits end: a workgroup waits only for columns to its left of its own tile, that is for
-// workgroups of smaller index, and each XCD starts its workgroups in index order, so the first
-// unfinished one waits for nothing.  Were that not to hold, a wait gives up after SPIN_MAX
-// loads, marks the fill as failed (the solve then returns RK_E_INTERNAL) and goes on.
+// Waits end: a workgroup waits only for columns to the left of its own in the same tile, and
+// which columns it takes is decided when it starts: the tile's next ones, by a counter per
+// tile.  So it waits only for workgroups that have started, in whatever order the XCDs
+// start them and whatever else runs beside (another fill of this kind on another stream too,
+// which could otherwise hold the place that a workgroup waited for needs).  As a last guard a
+// wait gives up after SPIN_MAX loads, marks the fill as failed (the solve then returns
+// RK_E_INTERNAL) and goes on.
 #include "rk_device.h"
 
 #include <algorithm>
@@ -74,13 +77,20 @@ __device__ inline int32_t *sum_at(const Tables &tb, int32_t e, int32_t r)
 }
 static_assert((int64_t)64 * RK_MAX_L * (RK_MAX_L + 1) / 2 < (int64_t(1) << 32), "summary words are counted in 32 bits");
 
-// Every entry of the span rows of opt from column 0 on: UNSET.
-__global__ __launch_bounds__(256) void k_tile_init(Tables tb)
+// How many workgroups of the running launch have started on tile sb: in the slack rows before
+// row 0, which nothing else of this fill uses.  The launch's last one sets it back to 0.
+__device__ inline int32_t *started_at(const Tables &tb, int32_t sb) { return tb.opt - SLACK * (int64_t)tb.stride + sb; }
+static_assert((RK_MAX_L + TB - 1) / TB <= SLACK * 64 && (RK_MAX_L + TB - 1) / TB <= 256,
+              "the counters fit the slack rows (a row has 64 words at least) and k_tile_init's workgroup");
+
+// Every entry of the span rows of opt from column 0 on: UNSET.  The counters: 0.
+__global__ __launch_bounds__(256) void k_tile_init(Tables tb, int32_t nb)
 {
     typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
     i32x4u *const row = (i32x4u *)(tb.opt + (int64_t)blockIdx.x * tb.stride);
     const i32x4u unset = {UNSET, UNSET, UNSET, UNSET};
     for (int32_t j = tb.padl / 4 + (int32_t)threadIdx.x; 4 * j < tb.stride; j += 256) row[j] = unset;
+    if (blockIdx.x == 0 && (int32_t)threadIdx.x < nb) *started_at(tb, (int32_t)threadIdx.x) = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[1] = 0;
 }
 
@@ -95,6 +105,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     __shared__ int32_t aps[(TRI + TB) * 64]; // left operands inside block S (reads run past a row's last)
     __shared__ int32_t win[NW ? TB * NW * 64 : 1];
     __shared__ int32_t prog[TB];             // rows each wave has finished
+    __shared__ int32_t taken;
     __shared__ uint16_t list[DIAG ? 1 : RK_MAX_L];  // the product's splits, less i0
     __shared__ int32_t n_kept, ubs[DIAG ? 1 : TB * TB], keep[RK_MAX_L / 32 + 1];
     static_assert(TCI == 4 && TB == 16, "a wave stages four rows of one split");
@@ -103,6 +114,14 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     const int32_t L = ch.L, K4 = ch.K4;
     int32_t chunk, sb;
     chunk_tile(blockIdx.x, (uint32_t)((L + TB - 1) / TB - level), &chunk, &sb);
+    if (threadIdx.x == 0) {
+        int32_t *const started = started_at(tb, sb);
+        taken = __hip_atomic_fetch_add(started, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (as many workgroups as chunk_grid launches for each tile)
+        if (taken == (n_chunks + 7) / 8 * 8 - 1) st_dev(0, started);
+    }
+    __syncthreads();
+    chunk = __builtin_amdgcn_readfirstlane(taken);
     if (chunk >= n_chunks) return;
     const int32_t lane = (int32_t)(threadIdx.x & 63);
     const int32_t lt = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
@@ -508,7 +527,7 @@ hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hip
         {k_tile<false, 0>, k_tile<false, 1>, k_tile<false, 2>, k_tile<false, 3>, k_tile<false, 4>},
         {k_tile<true, 0>, k_tile<true, 1>, k_tile<true, 2>, k_tile<true, 3>, k_tile<true, 4>}};
     static_assert(TWIN == 4, "one kernel per window width");
-    hipLaunchKernelGGL(k_tile_init, dim3((uint32_t)n_rows(ch.L)), dim3(256), 0, stream, tb);
+    hipLaunchKernelGGL(k_tile_init, dim3((uint32_t)n_rows(ch.L)), dim3(256), 0, stream, tb, nb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int32_t level = 0; level < nb; ++level) {

@@ -79,3 +79,27 @@ def test_two_chains_at_once_on_two_streams():
     finally:
         for s in solvers:
             s.close()
+
+
+def test_many_workgroups_of_two_fills_at_once():
+    """Two fills of more workgroups per launch than the chip holds, on two streams: each waits
+    only for workgroups of its own that have started."""
+    import torch
+    ch = make_random_chain(77, 128, 3, M=9000, xmax=60, amax=300, tmax=9)
+    solvers = [rk.Solver(ch) for _ in range(2)]
+    try:
+        want = solvers[0].solve()
+        curve = solvers[0].tradeoff_curve()
+        n = solvers[0].workspace_bytes(ch.M)
+        ws = [torch.empty(n, dtype=torch.uint8, device="cuda:0") for _ in solvers]
+        st = [torch.cuda.Stream() for _ in solvers]
+        for rep in range(3):
+            say(f"  round {rep}")
+            for s, w, q in zip(solvers, ws, st):
+                s.solve_async(ch.M, w.data_ptr(), n, q.cuda_stream)
+            for s in solvers:
+                assert s.result() == want
+                assert np.array_equal(s.tradeoff_curve(), curve)
+    finally:
+        for s in solvers:
+            s.close()
