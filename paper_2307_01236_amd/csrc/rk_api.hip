@@ -60,6 +60,9 @@ struct rk_chain {
     int32_t *host = nullptr;   // Tables::host
     int64_t *bt_res = nullptr; // backtrace: steps, first backward, status
     bool tiled = false;       // the last fill ran by tiles (its answer is in host[0])
+    // A fill of this chain lies in a graph of a caller's, whose replays also write host[0], at any
+    // time and for that fill's budget: answers are then read from the last fill's own table.
+    bool replayable = false;
     int32_t *rowbuf = nullptr;  // a row: its values, then its codes
     int32_t rowbuf_cap = 0;
 };
@@ -288,6 +291,7 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
     hipStreamCaptureStatus scs = hipStreamCaptureStatusNone;
     HIPCHK(hipStreamIsCapturing(stream, &scs));
     c->in_caller_graph = scs != hipStreamCaptureStatusNone;
+    c->replayable |= c->in_caller_graph;
     if (!c->in_caller_graph) HIPCHK(hipEventRecord(c->ev_fill0, stream));
     const bool replay = c->gexec && c->g_M == M && c->g_tables == tables && c->g_stream == stream &&
                         c->g_prof == c->prof.on;
@@ -344,7 +348,7 @@ int answer(rk_chain *c, int32_t *out)
     HIPCHK(wait_fill(c));
     if (c->tiled && c->host[1]) return RK_E_INTERNAL;
     if (c->M < c->h.x[0]) { *out = RK_INF; return RK_OK; }
-    if (c->tiled) { *out = to_abi(c->host[0]); return RK_OK; }
+    if (c->tiled && !c->replayable) { *out = to_abi(c->host[0]); return RK_OK; }
     int32_t v = 0;
     const int64_t idx = rk::row_of(c->h.L, 0, c->h.L - 1) * c->tb.stride + c->tb.padl + (c->M - c->h.x[0]);
     HIPCHK(hipMemcpy(&v, c->tb.opt + idx, sizeof(int32_t), hipMemcpyDeviceToHost));

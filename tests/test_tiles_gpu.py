@@ -103,3 +103,29 @@ def test_many_workgroups_of_two_fills_at_once():
     finally:
         for s in solvers:
             s.close()
+
+
+def test_answer_of_the_last_solve_after_a_replay():
+    """A captured fill at one budget, replayed after a solve at another: the answer asked for
+    is the last solve's."""
+    import torch
+    ch = make_random_chain(41, 20, 3, M=120, xmax=5, amax=12, tmax=9)
+    full = oracle.solve(ch).answer
+    low, less = next((m, v) for m in range(ch.M - 1, 0, -1) for v in [oracle.solve(ch, m).answer] if v != full)
+    s = rk.Solver(ch)
+    try:
+        n = s.workspace_bytes(ch.M)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        st = torch.cuda.Stream()
+        assert s.solve() == full
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            s.solve_async(ch.M, ws.data_ptr(), n, st.cuda_stream)
+        for rep in range(3):
+            assert s.solve(low) == less
+            g.replay()
+            torch.cuda.synchronize()
+            say(f"  replay {rep}")
+            assert s.result() == less
+    finally:
+        s.close()
