@@ -22,9 +22,9 @@
 // another workgroup's load 0.35-0.5 us later, on one XCD or across).
 //
 // Measured against one launch per diagonal (4.5-10 us each, mostly latency), fill time at blocks
-// x budgets x options: 8 x 501 x 3 42 -> 30 us, 64 x 1001 x 5 416 -> 170 us, 128 x 2001 x 8
-// 1.08 -> 0.46 ms, 256 x 4001 x 8 3.51 -> 2.13 ms, 384 x 6001 x 16 8.2 -> 6.4 ms, 1000 x 601 x 4
-// 24.7 -> 17.3 ms, 61 x 25002 x 4 1.05 -> 0.56 ms.
+// x budgets x options: 8 x 501 x 3 42 -> 20 us, 64 x 1001 x 5 416 -> 159 us, 128 x 2001 x 8
+// 1.08 -> 0.42 ms, 256 x 4001 x 8 3.51 -> 2.03 ms, 384 x 6001 x 16 8.2 -> 5.9 ms, 1000 x 601 x 4
+// 24.7 -> 16.9 ms.
 //
 // Waits end: a workgroup waits only for columns to the left of its own in the same tile, and
 // which columns it takes is decided when it starts: the tile's next ones, by a counter per
@@ -83,13 +83,21 @@ __device__ inline int32_t *started_at(const Tables &tb, int32_t sb) { return tb.
 static_assert((RK_MAX_L + TB - 1) / TB <= SLACK * 64 && (RK_MAX_L + TB - 1) / TB <= 256,
               "the counters fit the slack rows (a row has 64 words at least) and k_tile_init's workgroup");
 
-// Every entry of the span rows of opt from column 0 on: UNSET.  The counters: 0.
-__global__ __launch_bounds__(256) void k_tile_init(Tables tb, int32_t nb)
+// The entries of the span rows of opt that a workgroup may wait for: UNSET.  The counters: 0.
+// A workgroup that reads row r at other budgets does so only if its first column, less reach,
+// lies below msa(r) (else the row is flat there), so nobody waits for a column from
+// msa(r) + reach + 64 on.  Bound by its stores: the whole rows took 312 us at 384 blocks x 6001
+// budgets (5.8 TB/s), a pass there 6.31 -> 6.16 ms without the rest.  Rows that one store of
+// each thread covers are set whole: there the wait for msa costs more than the stores (1000
+// blocks x 601 budgets 17.6 -> 17.8 ms with it).
+__global__ __launch_bounds__(256) void k_tile_init(Tables tb, const int32_t *msa, int32_t reach, int32_t nb)
 {
     typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
     i32x4u *const row = (i32x4u *)(tb.opt + (int64_t)blockIdx.x * tb.stride);
     const i32x4u unset = {UNSET, UNSET, UNSET, UNSET};
-    for (int32_t j = tb.padl / 4 + (int32_t)threadIdx.x; 4 * j < tb.stride; j += 256) row[j] = unset;
+    int32_t end = tb.stride;
+    if (end - tb.padl > 4 * 256) end = (int32_t)min((int64_t)tb.padl + msa[blockIdx.x] + reach + 64, (int64_t)end);
+    for (int32_t j = tb.padl / 4 + (int32_t)threadIdx.x; 4 * j < end; j += 256) row[j] = unset;
     if (blockIdx.x == 0 && (int32_t)threadIdx.x < nb) *started_at(tb, (int32_t)threadIdx.x) = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[1] = 0;
 }
@@ -527,7 +535,7 @@ hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hip
         {k_tile<false, 0>, k_tile<false, 1>, k_tile<false, 2>, k_tile<false, 3>, k_tile<false, 4>},
         {k_tile<true, 0>, k_tile<true, 1>, k_tile<true, 2>, k_tile<true, 3>, k_tile<true, 4>}};
     static_assert(TWIN == 4, "one kernel per window width");
-    hipLaunchKernelGGL(k_tile_init, dim3((uint32_t)n_rows(ch.L)), dim3(256), 0, stream, tb, nb);
+    hipLaunchKernelGGL(k_tile_init, dim3((uint32_t)n_rows(ch.L)), dim3(256), 0, stream, tb, ch.msa, ch.reach, nb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int32_t level = 0; level < nb; ++level) {
