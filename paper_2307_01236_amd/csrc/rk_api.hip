@@ -60,8 +60,9 @@ struct rk_chain {
     int32_t *host = nullptr;   // Tables::host
     int64_t *bt_res = nullptr; // backtrace: steps, first backward, status
     bool tiled = false;       // the last fill ran by tiles (its answer is in host[0])
-    // A fill of this chain lies in a graph of a caller's, whose replays also write host[0], at any
-    // time and for that fill's budget: answers are then read from the last fill's own table.
+    // A fill of this chain lies in a graph of a caller's, whose replays also write host[0] and
+    // host[1], at any time and for that fill: the answer and whether the fill failed are then read
+    // from the last fill's own table.
     bool replayable = false;
     int32_t *rowbuf = nullptr;  // a row: its values, then its codes
     int32_t rowbuf_cap = 0;
@@ -346,7 +347,11 @@ int answer(rk_chain *c, int32_t *out)
 {
     if (!c->queued) return RK_E_NOT_SOLVED;
     HIPCHK(wait_fill(c));
-    if (c->tiled && c->host[1]) return RK_E_INTERNAL;
+    if (c->tiled) {
+        int32_t failed = c->host[1];
+        if (c->replayable) HIPCHK(hipMemcpy(&failed, rk::failed_at(c->tb), sizeof(int32_t), hipMemcpyDeviceToHost));
+        if (failed) return RK_E_INTERNAL;
+    }
     if (c->M < c->h.x[0]) { *out = RK_INF; return RK_OK; }
     if (c->tiled && !c->replayable) { *out = to_abi(c->host[0]); return RK_OK; }
     int32_t v = 0;
@@ -371,10 +376,10 @@ int read_row(rk_chain *c, int32_t s, int32_t t, bool codes)
         }
         c->rowbuf_cap = c->W;
     }
-    HIPCHK(rk::launch_read_row(c->dc, c->tb, s, t, c->rowbuf,
+    HIPCHK(rk::launch_read_row(c->dc, c->tb, s, t, c->tiled, c->rowbuf,
                                codes ? reinterpret_cast<int16_t *>(c->rowbuf + c->W) : nullptr, c->own_stream));
     HIPCHK(hipStreamSynchronize(c->own_stream));
-    return RK_OK;
+    return c->host[2] ? RK_E_INTERNAL : RK_OK;
 }
 
 }  // namespace
@@ -589,7 +594,6 @@ int rk_read_row(rk_chain *c, int32_t s, int32_t t, int32_t *opt_row, int16_t *ar
     DeviceScope ds(c);
     if (!ds.ok) return RK_E_DEVICE;
     HIPCHK(wait_fill(c));
-    if (c->tiled && c->host[1]) return RK_E_INTERNAL;
     int rc = read_row(c, s, t, arg_row != nullptr);
     if (rc != RK_OK) return rc;
     if (opt_row) std::copy(c->rowbuf, c->rowbuf + c->W, opt_row);
@@ -612,7 +616,6 @@ int rk_tradeoff_curve(rk_chain *c, int32_t *times, int64_t n)
     DeviceScope ds(c);
     if (!ds.ok) return RK_E_DEVICE;
     HIPCHK(wait_fill(c));
-    if (c->tiled && c->host[1]) return RK_E_INTERNAL;
     // budget b leaves b - x_0 slots beyond the chain input: Opt(0, L-1, b - x_0)
     const int64_t x0 = c->h.x[0], lead = std::min<int64_t>(n, x0);
     for (int64_t b = 0; b < lead; ++b) times[b] = RK_INF;

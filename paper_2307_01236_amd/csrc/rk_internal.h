@@ -127,9 +127,16 @@ struct Tables {
     unsigned long long *ctr;
     int32_t *rec;
     // Pinned host memory that the tiled fill writes: [0] the answer Opt(0, L-1, M - x_0), [1]
-    // whether the fill failed (a wait that gave up).
+    // whether the fill failed (a wait that gave up); and that k_read_row writes: [2] whether the
+    // fill of the table it read failed.
     int32_t *host;
 };
+
+// Whether a tiled fill of this table failed: a word of the slack rows before row 0, which each
+// such fill clears first.  It goes with the table, whoever fills it (a caller may replay a
+// captured fill of the same chain into another one).
+constexpr int32_t TABLE_FAILED = 256;
+__host__ __device__ inline int32_t *failed_at(const Tables &tb) { return tb.opt - SLACK * (int64_t)tb.stride + TABLE_FAILED; }
 
 // The finalize skip counter: a workgroup adds into slot blockIdx.x % CTR_SLOTS, the slots
 // CTR_PITCH counters (128 bytes) apart, so that the atomics spread over the L2 channels
@@ -192,9 +199,9 @@ hipError_t launch_fill(const DevChain &ch, const Tables &tb, hipStream_t stream,
 // The fill by square tiles (rk_tile.hip); m_ans: the answer's column (-1: none).
 hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hipStream_t stream, int32_t *launches);
 // Row (s, t) as the ABI shows it (codes: choice codes in option slots, or null); values and codes
-// are pinned host memory.
-hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, int32_t *values, int16_t *codes,
-                           hipStream_t stream);
+// are pinned host memory.  tiled: the table's fill was a tiled one.
+hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool tiled, int32_t *values,
+                           int16_t *codes, hipStream_t stream);
 // Alg. 3 on the device; ops and res are pinned host memory (ops past cap are counted, not
 // written); res[0] = number of steps, res[1] = index of the first
 // backward, res[2] = status (0 ok, 1 infeasible cell, 2 inconsistent table,

@@ -31,7 +31,7 @@
 // tile.  So it waits only for workgroups that have started, in whatever order the XCDs
 // start them and whatever else runs beside (another fill of this kind on another stream too,
 // which could otherwise hold the place that a workgroup waited for needs).  As a last guard a
-// wait gives up after SPIN_MAX loads, marks the fill as failed (the solve then returns
+// wait gives up after SPIN_MAX loads, marks the table as failed (reads of it then return
 // RK_E_INTERNAL) and goes on.
 #include "rk_device.h"
 
@@ -80,8 +80,9 @@ static_assert((int64_t)64 * RK_MAX_L * (RK_MAX_L + 1) / 2 < (int64_t(1) << 32), 
 // How many workgroups of the running launch have started on tile sb: in the slack rows before
 // row 0, which nothing else of this fill uses.  The launch's last one sets it back to 0.
 __device__ inline int32_t *started_at(const Tables &tb, int32_t sb) { return tb.opt - SLACK * (int64_t)tb.stride + sb; }
-static_assert((RK_MAX_L + TB - 1) / TB <= SLACK * 64 && (RK_MAX_L + TB - 1) / TB <= 256,
-              "the counters fit the slack rows (a row has 64 words at least) and k_tile_init's workgroup");
+static_assert((RK_MAX_L + TB - 1) / TB <= TABLE_FAILED && TABLE_FAILED < SLACK * 64 && TABLE_FAILED <= 256,
+              "the counters and the flag after them fit the slack rows (a row has 64 words at least), the counters "
+              "k_tile_init's workgroup");
 
 // The entries of the span rows of opt that a workgroup may wait for: UNSET.  The counters: 0.
 // A workgroup that reads row r at other budgets does so only if its first column, less reach,
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(256) void k_tile_init(Tables tb, const int32_t *msa
     if (end - tb.padl > 4 * 256) end = (int32_t)min((int64_t)tb.padl + msa[blockIdx.x] + reach + 64, (int64_t)end);
     for (int32_t j = tb.padl / 4 + (int32_t)threadIdx.x; 4 * j < end; j += 256) row[j] = unset;
     if (blockIdx.x == 0 && (int32_t)threadIdx.x < nb) *started_at(tb, (int32_t)threadIdx.x) = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[1] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[1] = *failed_at(tb) = 0;
 }
 
 // index in LDS of the left operand ap(s, s + u), s = 16 S + ls, u = 0 .. 14 - ls
@@ -320,7 +321,10 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         for (int32_t n = 0; get() && !dead;)
             if (++n > SPIN_MAX) {
                 dead = true;
-                if (lane == 0) __hip_atomic_store(tb.host + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                if (lane == 0) {
+                    st_dev(1, failed_at(tb));
+                    __hip_atomic_store(tb.host + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                }
             }
     };
     // wait for rows up to ls of the waves lo .. hi - 1 of this workgroup

@@ -129,3 +129,41 @@ def test_answer_of_the_last_solve_after_a_replay():
             assert s.result() == less
     finally:
         s.close()
+
+
+def test_failure_belongs_to_the_table_it_happened_in():
+    """A wait that gives up marks the table that was being filled (here the mark is planted: word
+    256 of the workspace).  Reads of that table are refused until it is filled again, whatever
+    replays of a captured fill do in another table; a mark in that other one means nothing to them."""
+    import torch
+    ch = make_random_chain(41, 20, 3, M=120, xmax=5, amax=12, tmax=9)
+    s = rk.Solver(ch)
+    try:
+        n = s.workspace_bytes(ch.M)
+        captured, last = (torch.empty(n // 4, dtype=torch.int32, device="cuda:0") for _ in range(2))
+        st = torch.cuda.Stream()
+        full = s.solve()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            s.solve_async(ch.M, captured.data_ptr(), n, st.cuda_stream)
+        g.replay()
+        torch.cuda.synchronize()
+        s.solve_async(ch.M, last.data_ptr(), n, st.cuda_stream)
+        assert s.result() == full
+        last[256] = 1
+        for rep in range(2):
+            torch.cuda.synchronize()
+            for read in (s.result, s.schedule, s.tradeoff_curve, lambda: s.row(0, 3)):
+                with pytest.raises(rk.RKError) as e:
+                    read()
+                assert e.value.code == rk.RK_E_INTERNAL
+            g.replay()  # a fill that does not fail, into the other table
+        torch.cuda.synchronize()
+        s.solve_async(ch.M, last.data_ptr(), n, st.cuda_stream)
+        captured[256] = 1
+        torch.cuda.synchronize()
+        assert s.result() == full
+        s.schedule(), s.tradeoff_curve(), s.row(0, 3)
+        assert int(last[256]) == 0
+    finally:
+        s.close()
