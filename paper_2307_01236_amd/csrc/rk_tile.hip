@@ -442,9 +442,10 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         for (int32_t u = TB - 1; u > 1; --u) os[u] = os[u - 1];
         finish(again);
         if constexpr (NW > 0) {
-            if (flat) {
+            if (flat) {  // (columns left of 0 stay infinite: a flat row has none here, no row may)
 #pragma unroll
-                for (int32_t k = 0; k < NW; ++k) wn[64 * k] = fv;
+                for (int32_t k = 0; k < NW; ++k)
+                    if (!DIAG || k >= k0) wn[64 * k] = fv;
             } else if (wait) {
 #pragma unroll
                 for (int32_t k = 0; k < NH; ++k)

@@ -37,6 +37,40 @@ def test_reach_of_case_1(reach):
     full_parity(ch, 900)
 
 
+@pytest.mark.parametrize("L,M,xmax,amax", [(16, 200, 70, 20), (21, 90, 9, 30), (33, 260, 30, 90), (36, 500, 90, 170)])
+def test_operand_tables(L, M, xmax, amax):
+    """The operands of the splits beside Opt: Opt(s, t, m - x_s), infinite for m < x_s, and
+    P(s, t+1) + Opt(s, t, m), infinite where the sweep does not fit; staged and unstaged shifts."""
+    import torch
+    ch = make_random_chain(900 + L, L, 3, M=M, xmax=xmax, amax=amax, tmax=9, tmin=0, allow_zero=True)
+    s = rk.Solver(ch)
+    try:
+        n = s.workspace_bytes(M)
+        ws = torch.zeros(n // 4, dtype=torch.int32, device="cuda:0")
+        s.solve_async(M, ws.data_ptr(), n, torch.cuda.Stream().cuda_stream)
+        s.result()
+        rows = L * (L + 1) // 2 + 65
+        opt, ap, os = ws.cpu().numpy().astype(np.int64).reshape(3, rows, -1)[:, 32:]
+        padl, inf = opt.shape[1] - (M + 1 + 63) // 64 * 64, (1 << 30) - 1
+        r = 0
+        for a in range(L):
+            need = total = 0
+            for b in range(a, L):
+                row = opt[r, padl : padl + M + 1] & inf
+                want = np.full(M + 1, inf)
+                want[ch.x[a] :] = row[: max(M + 1 - ch.x[a], 0)]
+                assert np.array_equal(os[r, padl : padl + M + 1], want), ("right", a, b)
+                total += int(ch.fn_time[b])
+                need = max(need, (int(ch.x[b]) if b > a else 0) + int(ch.x[b + 1]) + int(ch.fn_tmp[b]))
+                if b + 1 < L:
+                    want = np.minimum(total + row, inf)
+                    want[:need] = inf
+                    assert np.array_equal(ap[r, padl : padl + M + 1], want), ("left", a, b)
+                r += 1
+    finally:
+        s.close()
+
+
 def test_splits_sorted_out_in_pieces():
     """330 blocks: products of up to 305 splits, whose list of splits that matter is made in
     three pieces.  The fill by levels of diagonals (profiled solves) on the other side."""
