@@ -1447,7 +1447,8 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
 {
     extern __shared__ __align__(16) int32_t sh[];
     __shared__ i32x4 found[BT_WAVES];  // per wave: cost, code, entry of the next cell, entry of the left sub-span
-    __shared__ int32_t order[6];       // what the first wave wants: mode, s, t, m, steps, the cell's entry
+    __shared__ int32_t order[6];       // what the first wave wants: mode, s, t, m, steps, the cell's entry (-1: not known)
+    __shared__ int32_t cell_entry;     // the entry of a cell searched
     const int32_t L = ch.L, K = ch.K, K4 = ch.K4, tid = (int32_t)threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t stack_cap = bt_stack_cap(ch);
@@ -1550,7 +1551,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
             // cost more by that alone are not looked at.
             const int32_t known = ordered(5);
             const int32_t most = known < 0 ? INT32_MAX : (known & DINF) - (lbs[ct + 1] - lbs[cs]);
-            if (known < 0 && tid == 0) order[5] = entry(cs, ct, cm);
+            if (tid == 0) cell_entry = known < 0 ? entry(cs, ct, cm) : known;
             auto take = [&](bool ok, uint32_t v, int32_t code, int32_t nx, int32_t sd) {
                 const uint64_t key = ok && v < (uint32_t)DINF ? (uint64_t)v << 32 | (uint32_t)code : ~0ull;
                 if (key < best) best = key, next = nx, side = sd;
@@ -1652,7 +1653,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
         const int32_t next = __builtin_amdgcn_readlane(f.z, wl), side = __builtin_amdgcn_readlane(f.w, wl);
         have = false;
         if (cost >= (uint32_t)DINF) { status = 1; continue; }
-        if ((int32_t)cost != (order[5] & DINF)) { status = 2; continue; }
+        if ((int32_t)cost != (cell_entry & DINF)) { status = 2; continue; }
         if (sp + 4 > stack_cap) { status = 3; continue; }
         if (code >= (uint32_t)(L + K)) {
             // case 3: F_s^o keeps its data; the sweep s+1..i-1 to x_i, where i is H's choice at
