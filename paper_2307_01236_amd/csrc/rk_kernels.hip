@@ -1440,7 +1440,11 @@ static int32_t bt_steps(const DevChain &ch)
     return ch.c3 || n < 3 ? 1 : n;
 }
 
-template <bool OPTS_LDS>
+// SWEEP: with the saving sweep, whose fill marks no cell, so that every one is searched; a span of up to
+// 65 blocks with up to 64 options then by the first wave alone, without a barrier (schedules of 64-1000
+// blocks: one wave for every span 158-2290 us, all waves 177-2500 us, this 131-1810 us).  Without the
+// sweep that is left out: beside it the steps of the walk take 5 % longer.
+template <bool OPTS_LDS, bool SWEEP>
 __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb, int32_t m_top, int32_t steps,
                                                           rk_op *__restrict__ ops, int64_t cap,
                                                           int64_t *__restrict__ res)
@@ -1452,7 +1456,6 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
     const int32_t L = ch.L, K = ch.K, K4 = ch.K4, tid = (int32_t)threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t stack_cap = bt_stack_cap(ch);
-    const bool sweep = ch.c3 != nullptr;
     Frame *const stk = reinterpret_cast<Frame *>(sh);
     // options of every block (xbar, r(F)+r(B), need1): in LDS where they fit
     i32x4 *const lo = reinterpret_cast<i32x4 *>(sh + 4 * stack_cap);
@@ -1490,30 +1493,159 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
     };
     auto push = [&](Frame f) { stk[sp] = f; ++sp; };
 
+    // the first wave: act on the choice (cost, code, entry of the next cell, entry of the left sub-span)
+    // found at (s, t, m), whose entry is `stored`
+    auto scalar = [](int32_t v) { return SWEEP ? __builtin_amdgcn_readfirstlane(v) : v; };
+    auto resolve = [&](i32x4 choice, int32_t stored) {
+        const uint32_t cost = (uint32_t)choice.x, code = (uint32_t)choice.y;
+        have = false;
+        if (cost >= (uint32_t)DINF) { status = 1; return; }
+        if ((int32_t)cost != (scalar(stored) & DINF)) { status = 2; return; }
+        if (sp + 4 > stack_cap) { status = 3; return; }
+        int32_t s_next, m_next, own_next = choice.z;  // (assigned once, below: else the state ends up in scratch memory)
+        if (SWEEP && code >= (uint32_t)(L + K)) {
+            // case 3: F_s^o keeps its data; the sweep s+1..i-1 to x_i, where i is H's choice at
+            // (s+1, t, u = m - mem); then i..t, x_i dropped, x_{s+1} made again from the kept
+            // data, s+1..i-1, and B_s^o
+            const int32_t o = (int32_t)code - L - K, s1 = s + 1;
+            const int32_t xb = scalar(option(s * K4 + o).x), x1 = scalar(xs[s1]);
+            const int32_t u = m - (xb - x1);
+            const int32_t hown = scalar(tb.hopt[row_of(L, s1, t) * stride + padl + u]);
+            const int32_t *const aq_s = tb.aq + row_of(L, s1, s1) * stride + padl + u - min(x1, padl);
+            uint64_t hb = ~0ull;
+            for (int32_t j = lane; j < t - s1; j += 64) {  // split i = s1 + 1 + j, code i
+                const int32_t i = s1 + 1 + j;
+                const int32_t a = aq_s[j * stride];
+                const int32_t q = tb.opt[row_of(L, i, t) * stride + (padl + u - min(xs[i], padl))];
+                hb = min(hb, ((uint64_t)((uint32_t)a + (uint32_t)q) << 32) | (uint32_t)i);
+            }
+            const uint32_t hc = (uint32_t)(hb >> 32), hk = (uint32_t)hb;
+            const uint32_t hcost = wave_min_u32(hc);
+            const int32_t i = (int32_t)wave_min_u32(hc == hcost ? hk : ~0u);
+            if ((int32_t)hcost != hown || hcost >= (uint32_t)DINF || i <= s1 || i > t) { status = 2; return; }
+            emit(RK_FWD_SAVE, s, o);
+            for (int32_t k = lane; k < i - s - 1; k += 64) {
+                const int64_t at = n + 2 * (int64_t)k;
+                if (at < cap) ops[at] = rk_op{RK_FWD_NOSAVE, s1 + k, -1};
+                if (at + 1 < cap) ops[at + 1] = rk_op{RK_FREE_X, s1 + k, -1};
+            }
+            n += 2 * (int64_t)(i - s - 1);
+            push(Frame{1, RK_BWD, s, o});
+            push(Frame{0, s1 | (i - 1) << 11, m - xb, -1});
+            push(Frame{1, RK_REFWD, s, o});
+            push(Frame{1, RK_FREE_X, i, -1});
+            s_next = i;
+            m_next = u - scalar(xs[i]);
+            own_next = -1;
+        } else if (code >= (uint32_t)L) {
+            const int32_t o = (int32_t)code - L;
+            emit(RK_FWD_SAVE, s, o);
+            push(Frame{1, RK_BWD, s, o});
+            s_next = s + 1;
+            m_next = m - scalar(option(s * K4 + o).x);
+        } else {
+            // forward through blocks s..i-1 keeping nothing, dropping x_{s+1}..x_{i-1} behind
+            const int32_t i = (int32_t)code;
+            emit(RK_FWD_NOSAVE, s, -1);
+            for (int32_t k = lane; k < i - s - 1; k += 64) {
+                const int64_t at = n + 2 * (int64_t)k;
+                if (at < cap) ops[at] = rk_op{RK_FWD_NOSAVE, s + 1 + k, -1};
+                if (at + 1 < cap) ops[at + 1] = rk_op{RK_FREE_X, s + 1 + k, -1};
+            }
+            n += 2 * (int64_t)(i - s - 1);
+            push(Frame{0, s | (i - 1) << 11, m, choice.w});
+            push(Frame{1, RK_FREE_X, i, -1});
+            s_next = i;
+            m_next = m - scalar(xs[i]);
+        }
+        s = s_next;
+        m = m_next;
+        own = own_next;
+        have = s <= t;
+    };
+    // One cell (cs, ct, cm) searched by lanes that each take the splits
+    // i = cs + 1 + c, every cstep-th, and the options o, every ostep-th; the smallest (cost, code) of the
+    // wave's, with the entries of the next cell and the left sub-span.  All loads of a split and an
+    // option go out together.  A split costs at least lb(s,t) + P(s,i): where the cell's value is known
+    // (known >= 0), those that cost more by that alone are not looked at.
+    auto search = [&](int32_t cs, int32_t ct, int32_t cm, int32_t known, int32_t c, int32_t cstep, int32_t o,
+                      int32_t ostep) -> i32x4 {
+        uint64_t best = ~0ull;
+        int32_t next = 0, side = 0;
+        const int32_t d = ct - cs;
+        const int32_t most = known < 0 ? INT32_MAX : (known & DINF) - (lbs[ct + 1] - lbs[cs]);
+        auto take = [&](bool ok, uint32_t v, int32_t code, int32_t nx, int32_t sd) {
+            const uint64_t key = ok && v < (uint32_t)DINF ? (uint64_t)v << 32 | (uint32_t)code : ~0ull;
+            if (key < best) best = key, next = nx, side = sd;
+        };
+        const uint32_t ustride = (uint32_t)stride;
+        const int64_t below = row_of(L, min(cs + 1, ct), ct) * stride + padl;
+        const int32_t *const left = tb.opt + row_of(L, cs, cs) * stride + padl + cm, *const right = tb.opt + ct * stride + padl;
+        const int32_t x1 = xs[cs + 1];
+        auto row32 = [&](int32_t i) { return (uint32_t)(i * L - ((i * (i - 1)) >> 1) - i); };
+        for (; c < d || o < K; c += cstep, o += ostep) {
+            const int32_t i = cs + 1 + min(c, d), x = xs[i], p = fs[i] - fs[cs];
+            const bool split = c < d && p <= most, opt = o < K;
+            int32_t need = 0, l = DINF, r = DINF, v = 0, h = DINF, c3 = 0;
+            i32x4 q = {};
+            if (split) {
+                need = ch.need2[cs * L + i];
+                l = left[(uint64_t)(uint32_t)c * ustride];
+                r = right[(uint64_t)row32(i) * ustride + (uint32_t)max(cm - x, 0)];
+            }
+            if (opt) {
+                q = option(cs * K4 + o);
+                v = tb.opt[below + max(cm - q.x, 0)];
+                // case 3: c3 + H(s+1, t, m - mem), mem = xbar - x_{s+1}
+                if (SWEEP) h = tb.hopt[below + min(max(cm - (q.x - x1), 0), tb.W - 1)], c3 = ch.c3[cs * K + o];
+            }
+            take(split && cm >= need && (l & DINF) < DINF && (r & DINF) < DINF,
+                 (uint32_t)(l & DINF) + (uint32_t)(r & DINF) + (uint32_t)p, i, r, l);
+            const int32_t rest = d > 0 ? v : 0;
+            const bool ok = opt && cm >= q.z;
+            take(ok && (rest & DINF) < DINF, (uint32_t)q.y + (uint32_t)(rest & DINF), L + o, rest, 0);
+            take(SWEEP && ok && d >= 2 && h < DINF, (uint32_t)c3 + (uint32_t)h, L + K + o, -1, 0);
+        }
+        const uint32_t bc = (uint32_t)(best >> 32), bk = (uint32_t)best;
+        const uint32_t cost = wave_min_u32(bc), code = wave_min_u32(bc == cost ? bk : ~0u);
+        const int32_t wl = (int32_t)__builtin_ctzll(__ballot(bc == cost && bk == code));  // (no candidate: every lane the same)
+        return i32x4{(int32_t)cost, (int32_t)code, __builtin_amdgcn_readlane(next, wl), __builtin_amdgcn_readlane(side, wl)};
+    };
+    if constexpr (SWEEP) __syncthreads();  // (the first wave may search before the loop's first barrier)
+
     for (;;) {
         int32_t mode = SEARCH, ns = 0;
         if (wave == 0) {
-            while (!have && sp > 0) {  // emit the run of steps on top of the stack, or take its cell
-                const Frame f = stk[max(sp - 1 - lane, 0)];
-                const uint64_t cells = __ballot(lane < sp && f.type == 0);
-                const int32_t run = min(cells ? (int32_t)__builtin_ctzll(cells) : 64, sp);
-                if (lane < run && n + lane < cap) ops[n + lane] = rk_op{f.a, f.b, f.c};
-                const uint64_t bwd = __ballot(lane < run && f.a == RK_BWD);
-                if (nfwd < 0 && bwd) nfwd = n + __builtin_ctzll(bwd);
-                n += run;
-                sp -= run;
-                if (run == 0) {
-                    const int32_t a = __builtin_amdgcn_readfirstlane(f.a);
-                    s = a & 2047;
-                    t = a >> 11;
-                    m = __builtin_amdgcn_readfirstlane(f.b);
-                    own = __builtin_amdgcn_readfirstlane(f.c);
-                    --sp;
-                    have = true;
+            for (;;) {
+                while (!have && sp > 0) {  // emit the run of steps on top of the stack, or take its cell
+                    const Frame f = stk[max(sp - 1 - lane, 0)];
+                    const uint64_t cells = __ballot(lane < sp && f.type == 0);
+                    const int32_t run = min(cells ? (int32_t)__builtin_ctzll(cells) : 64, sp);
+                    if (lane < run && n + lane < cap) ops[n + lane] = rk_op{f.a, f.b, f.c};
+                    const uint64_t bwd = __ballot(lane < run && f.a == RK_BWD);
+                    if (nfwd < 0 && bwd) nfwd = n + __builtin_ctzll(bwd);
+                    n += run;
+                    sp -= run;
+                    if (run == 0) {
+                        const int32_t a = __builtin_amdgcn_readfirstlane(f.a);
+                        s = a & 2047;
+                        t = a >> 11;
+                        m = __builtin_amdgcn_readfirstlane(f.b);
+                        own = __builtin_amdgcn_readfirstlane(f.c);
+                        --sp;
+                        have = true;
+                    }
                 }
+                if (!have || status) mode = DONE;
+                else if (!SWEEP && own >= 0 && (own & ONLY_CASE1)) mode = WALK;
+                if constexpr (SWEEP)
+                    if (mode == SEARCH && t - s <= 64 && K <= 64) {
+                        const int32_t stored = own < 0 ? entry(s, t, m) : own;
+                        resolve(search(s, t, m, own, lane, 64, lane, 64), stored);
+                        continue;
+                    }
+                break;
             }
-            if (!have || status) mode = DONE;
-            else if (own >= 0 && (own & ONLY_CASE1)) mode = WALK;
             ns = min(steps > 1 ? steps : 64, t - s + 1);
             if (lane == 0) order[0] = mode, order[1] = s, order[2] = t, order[3] = m, order[4] = ns, order[5] = own;
         }
@@ -1522,7 +1654,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
         mode = ordered(0);
         if (mode == DONE) break;
         const int32_t cs = ordered(1), ct = ordered(2), cm = ordered(3);
-        if (mode == WALK) {
+        if (!SWEEP && mode == WALK) {
             const int32_t nr = ordered(4);
             if (steps == 1) {
                 __syncthreads();  // (the first wave fetches as it walks)
@@ -1543,57 +1675,17 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
                 __syncthreads();
             }
         } else {
-            // this thread's smallest (cost, code) over its candidates: splits i = s+1+c, then options
-            uint64_t best = ~0ull;
-            int32_t next = 0, side = 0;
-            const int32_t d = ct - cs;
-            // A split costs at least lb(s,t) + P(s,i): where the cell's value is known, those that
-            // cost more by that alone are not looked at.
-            const int32_t known = ordered(5);
-            const int32_t most = known < 0 ? INT32_MAX : (known & DINF) - (lbs[ct + 1] - lbs[cs]);
-            if (tid == 0) cell_entry = known < 0 ? entry(cs, ct, cm) : known;
-            auto take = [&](bool ok, uint32_t v, int32_t code, int32_t nx, int32_t sd) {
-                const uint64_t key = ok && v < (uint32_t)DINF ? (uint64_t)v << 32 | (uint32_t)code : ~0ull;
-                if (key < best) best = key, next = nx, side = sd;
-            };
-            // (all loads of a candidate in one round trip, at clamped addresses; rows (s, i-1) are
-            // consecutive, row (i, t) is row32(i) + t, below 2^32)
-            const uint32_t ustride = (uint32_t)stride;
-            const int32_t *const left = tb.opt + row_of(L, cs, cs) * stride + padl + cm;
-            const int32_t *const right = tb.opt + ct * stride + padl, *const below = tb.opt + row_of(L, min(cs + 1, ct), ct) * stride + padl;
-            auto row32 = [&](int32_t i) { return (uint32_t)(i * L - ((i * (i - 1)) >> 1) - i); };
             // (splits and options on waves of their own, so that no wave waits for both)
-            if (wave < BT_SPLIT_WAVES) {
-                for (int32_t c = tid; c < d; c += 64 * BT_SPLIT_WAVES) {
-                    const int32_t i = cs + 1 + c, x = xs[i], p = fs[i] - fs[cs];
-                    if (p > most) continue;
-                    const int32_t need = ch.need2[cs * L + i];
-                    const int32_t l = left[(uint64_t)(uint32_t)c * ustride], r = right[(uint64_t)row32(i) * ustride + (uint32_t)max(cm - x, 0)];
-                    take(cm >= need && (l & DINF) < DINF && (r & DINF) < DINF,
-                         (uint32_t)(l & DINF) + (uint32_t)(r & DINF) + (uint32_t)p, i, r, l);
-                }
-            } else {
-                const int32_t *const hbelow = sweep ? tb.hopt + row_of(L, min(cs + 1, ct), ct) * stride + padl : below;
-                const int32_t x1 = xs[min(cs + 1, L)];
-                for (int32_t o = tid - 64 * BT_SPLIT_WAVES; o < K; o += BT_THREADS - 64 * BT_SPLIT_WAVES) {
-                    const i32x4 q = option(cs * K4 + o);
-                    const int32_t v = below[(uint32_t)max(cm - q.x, 0)];
-                    // case 3: c3 + H(s+1, t, m - mem), mem = xbar - x_{s+1}
-                    const int32_t h = sweep ? hbelow[(uint32_t)min(max(cm - (q.x - x1), 0), tb.W - 1)] : DINF;
-                    const int32_t c3 = sweep ? ch.c3[cs * K + o] : 0;
-                    const int32_t r = d > 0 ? v : 0;
-                    const bool ok = cm >= q.z;
-                    take(ok && (r & DINF) < DINF, (uint32_t)q.y + (uint32_t)(r & DINF), L + o, r, 0);
-                    if (d >= 2) take(ok && h < DINF, (uint32_t)c3 + (uint32_t)h, L + K + o, -1, 0);
-                }
-            }
-            const uint32_t bc = (uint32_t)(best >> 32), bk = (uint32_t)best;
-            const uint32_t cost = wave_min_u32(bc), code = wave_min_u32(bc == cost ? bk : ~0u);
-            if (bc == cost && bk == code) found[wave] = i32x4{(int32_t)cost, (int32_t)code, next, side};  // (no candidate: every lane the same)
+            const int32_t known = ordered(5);
+            if (tid == 0) cell_entry = known < 0 ? entry(cs, ct, cm) : known;
+            const i32x4 f = wave < BT_SPLIT_WAVES
+                                ? search(cs, ct, cm, known, tid, 64 * BT_SPLIT_WAVES, K, 0)
+                                : search(cs, ct, cm, known, ct - cs, 0, tid - 64 * BT_SPLIT_WAVES, BT_THREADS - 64 * BT_SPLIT_WAVES);
+            if (lane == 0) found[wave] = f;
             __syncthreads();
         }
         if (wave != 0) continue;
-        if (mode == WALK) {
+        if (!SWEEP && mode == WALK) {
             // per step the smallest option that reaches own, one option per lane; the step's
             // operations are written after the walk, one step per lane
             const int32_t s0 = s;
@@ -1651,70 +1743,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_backtrace(DevChain ch, Tables tb
         const uint32_t cost = wave_min_u32(bc), code = wave_min_u32(bc == cost ? bk : ~0u);
         const int32_t wl = (int32_t)__builtin_ctzll(__ballot(bc == cost && bk == code));
         const int32_t next = __builtin_amdgcn_readlane(f.z, wl), side = __builtin_amdgcn_readlane(f.w, wl);
-        have = false;
-        if (cost >= (uint32_t)DINF) { status = 1; continue; }
-        if ((int32_t)cost != (cell_entry & DINF)) { status = 2; continue; }
-        if (sp + 4 > stack_cap) { status = 3; continue; }
-        if (code >= (uint32_t)(L + K)) {
-            // case 3: F_s^o keeps its data; the sweep s+1..i-1 to x_i, where i is H's choice at
-            // (s+1, t, u = m - mem); then i..t, x_i dropped, x_{s+1} made again from the kept
-            // data, s+1..i-1, and B_s^o
-            const int32_t o = (int32_t)code - L - K, s1 = s + 1;
-            const int32_t xb = option(s * K4 + o).x;
-            const int32_t u = m - (xb - xs[s1]);
-            const int32_t hown = tb.hopt[row_of(L, s1, t) * stride + padl + u];
-            const int32_t *const aq_s = tb.aq + row_of(L, s1, s1) * stride + padl + u - min(xs[s1], padl);
-            uint64_t hb = ~0ull;
-            for (int32_t j = lane; j < t - s1; j += 64) {  // split i = s1 + 1 + j, code i
-                const int32_t i = s1 + 1 + j;
-                const int32_t a = aq_s[j * stride];
-                const int32_t q = tb.opt[row_of(L, i, t) * stride + (padl + u - min(xs[i], padl))];
-                hb = min(hb, ((uint64_t)((uint32_t)a + (uint32_t)q) << 32) | (uint32_t)i);
-            }
-            const uint32_t hc = (uint32_t)(hb >> 32), hk = (uint32_t)hb;
-            const uint32_t hcost = wave_min_u32(hc);
-            const int32_t i = (int32_t)wave_min_u32(hc == hcost ? hk : ~0u);
-            if ((int32_t)hcost != hown || hcost >= (uint32_t)DINF || i <= s1 || i > t) { status = 2; continue; }
-            emit(RK_FWD_SAVE, s, o);
-            for (int32_t k = lane; k < i - s - 1; k += 64) {
-                const int64_t at = n + 2 * (int64_t)k;
-                if (at < cap) ops[at] = rk_op{RK_FWD_NOSAVE, s1 + k, -1};
-                if (at + 1 < cap) ops[at + 1] = rk_op{RK_FREE_X, s1 + k, -1};
-            }
-            n += 2 * (int64_t)(i - s - 1);
-            push(Frame{1, RK_BWD, s, o});
-            push(Frame{0, s1 | (i - 1) << 11, m - xb, -1});
-            push(Frame{1, RK_REFWD, s, o});
-            push(Frame{1, RK_FREE_X, i, -1});
-            have = true;
-            s = i;
-            m = u - xs[i];
-            own = -1;
-        } else if (code >= (uint32_t)L) {
-            const int32_t o = (int32_t)code - L;
-            emit(RK_FWD_SAVE, s, o);
-            push(Frame{1, RK_BWD, s, o});
-            have = t > s;
-            m -= option(s * K4 + o).x;
-            s += 1;
-            own = next;
-        } else {
-            // forward through blocks s..i-1 keeping nothing, dropping x_{s+1}..x_{i-1} behind
-            const int32_t i = (int32_t)code;
-            emit(RK_FWD_NOSAVE, s, -1);
-            for (int32_t k = lane; k < i - s - 1; k += 64) {
-                const int64_t at = n + 2 * (int64_t)k;
-                if (at < cap) ops[at] = rk_op{RK_FWD_NOSAVE, s + 1 + k, -1};
-                if (at + 1 < cap) ops[at + 1] = rk_op{RK_FREE_X, s + 1 + k, -1};
-            }
-            n += 2 * (int64_t)(i - s - 1);
-            push(Frame{0, s | (i - 1) << 11, m, side});
-            push(Frame{1, RK_FREE_X, i, -1});
-            have = true;
-            s = i;
-            m -= xs[i];
-            own = next;
-        }
+        resolve(i32x4{(int32_t)cost, (int32_t)code, next, side}, cell_entry);
     }
     if (tid == 0) {
         res[0] = n;
@@ -1732,8 +1761,10 @@ hipError_t launch_backtrace(const DevChain &ch, const Tables &tb, int32_t m_top,
     const size_t opts = sizeof(i32x4) * (size_t)ch.L * ch.K4;
     const bool in_lds = lds + opts <= BT_LDS;
     if (in_lds) lds += opts;
-    hipLaunchKernelGGL(in_lds ? k_backtrace<true> : k_backtrace<false>, dim3(1), dim3(BT_THREADS), lds, stream, ch, tb,
-                       m_top, steps, ops, cap, res);
+    static constexpr decltype(&k_backtrace<true, true>) kernels[2][2] = {{k_backtrace<false, false>, k_backtrace<false, true>},
+                                                                        {k_backtrace<true, false>, k_backtrace<true, true>}};
+    hipLaunchKernelGGL(kernels[in_lds][ch.c3 != nullptr], dim3(1), dim3(BT_THREADS), lds, stream, ch, tb, m_top, steps, ops, cap,
+                       res);
     return hipGetLastError();
 }
 

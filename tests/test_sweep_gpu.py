@@ -114,3 +114,20 @@ def test_sweep_lowers_answers_and_schedules_replay():
             s.close()
             t.close()
     assert found
+
+
+@pytest.mark.parametrize("L,K", [(64, 64), (65, 65), (66, 64), (67, 3), (70, 70)])
+def test_schedule_search_edges(L, K):
+    """Schedules of spans and option counts around those that the backtrace's first wave searches
+    alone (spans of up to 65 blocks, up to 64 options), at a tight and at a wide budget."""
+    ch = with_refwd(make_random_chain(8800 + L, L, K, xmax=6, amax=12, tmax=5, tmin=0), L, 0.0, 0.3)
+    mf = int(oracle.min_feasible(ch)[oracle.cell_index(L)[0, L - 1]] + ch.x[0])
+    for M in (mf + 4, mf + 60):
+        sol = oracle.solve(ch, M)
+        s = rk.Solver(ch)
+        try:
+            s.set_option_pruning(False)
+            assert s.solve(M) == sol.answer
+            check_same_schedule(s, sol, ch, M)
+        finally:
+            s.close()
