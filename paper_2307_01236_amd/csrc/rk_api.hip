@@ -51,10 +51,11 @@ struct rk_chain {
     hipStream_t g_stream = nullptr;
     bool g_prof = false;
 
-    rk_op *ops = nullptr;  // backtrace output: pinned
+    std::vector<rk_op> schedule;  // of the solve number bt_fill
+    int64_t fills = 0;            // solves queued so far
+    int64_t bt_fill = -1;
+    rk_op *ops = nullptr;  // backtrace output, pinned: for schedules that no Stage holds
     int64_t ops_cap = 0;
-    int64_t fills = 0;     // solves queued so far
-    int64_t bt_fill = -1;  // the solve whose schedule ops holds
     // Results come back through pinned host memory that the kernels write, so that a call waits
     // once (a blocking copy into pageable memory takes 15-20 us).
     int32_t *host = nullptr;   // Tables::host
@@ -64,8 +65,6 @@ struct rk_chain {
     // host[1], at any time and for that fill: the answer and whether the fill failed are then read
     // from the last fill's own table.
     bool replayable = false;
-    int32_t *rowbuf = nullptr;  // a row: its values, then its codes
-    int32_t rowbuf_cap = 0;
 };
 
 // Wait for the last fill queued by the library.  A fill inside the caller's graph runs when
@@ -123,6 +122,46 @@ int geometry(const rk_chain *c, int32_t M, Geometry *g, size_t *bytes)
     *bytes = (size_t)elems * sizeof(int32_t);
     return RK_OK;
 }
+
+// Pinned memory through which schedules and rows come back.  A call borrows a block, so that no
+// chain pays for one (hipHostMalloc takes 30-500 us: with buffers of its own, a chain's first curve
+// took 50-600 us where 20 do, its first schedule up to 0.6 ms longer).  A block given back is kept
+// for the next call, at most STAGES_KEPT of them until the process ends; set-up sees to the first.
+constexpr size_t STAGE_BYTES = (size_t)1 << 20;
+constexpr int STAGES_KEPT = 4;
+std::mutex g_stage_mu;
+void *g_stages[STAGES_KEPT];
+int g_n_stages = 0;
+
+struct Stage {
+    void *p = nullptr;
+    bool idle = true;  // no kernel may still write to the block
+    Stage()
+    {
+        {
+            std::lock_guard<std::mutex> lk(g_stage_mu);
+            if (g_n_stages > 0) p = g_stages[--g_n_stages];
+        }
+        if (!p && hipHostMalloc(&p, STAGE_BYTES, hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+    }
+    ~Stage()
+    {
+        if (!p || !idle) return;  // (a block whose kernel failed is never used again)
+        {
+            std::lock_guard<std::mutex> lk(g_stage_mu);
+            if (g_n_stages < STAGES_KEPT) {
+                g_stages[g_n_stages++] = p;
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+    Stage(const Stage &) = delete;
+    Stage &operator=(const Stage &) = delete;
+};
 
 // First solve on a device (or the first after the pruning switch changed): upload the
 // derived arrays; create the events and streams once.
@@ -211,6 +250,7 @@ int upload(rk_chain *c)
         }
         c->bt_res = reinterpret_cast<int64_t *>(c->host + 4);
     }
+    Stage first;  // the process has one from here on
     return RK_OK;
 }
 
@@ -361,25 +401,67 @@ int answer(rk_chain *c, int32_t *out)
     return RK_OK;
 }
 
-// Row (s, t) of the last solve, which is complete, into the pinned row buffer, waiting for it (on
-// the chain's own stream: the caller's may be gone by now).
-int read_row(rk_chain *c, int32_t s, int32_t t, bool codes)
+// Columns 0 .. n - 1 of row (s, t) of the last solve, which is complete, as the ABI shows them (values
+// and codes may be null), on the chain's own stream: the caller's may be gone by now.
+int read_row(rk_chain *c, int32_t s, int32_t t, int32_t n, int32_t *values, int16_t *codes)
 {
-    if (c->rowbuf_cap < c->W) {
-        if (c->rowbuf) HIPCHK(hipHostFree(c->rowbuf));
-        c->rowbuf = nullptr;
-        c->rowbuf_cap = 0;
-        if (hipHostMalloc(&c->rowbuf, (size_t)c->W * 6 + 64, hipHostMallocDefault) != hipSuccess) {
+    Stage stage;
+    if (!stage.p) return RK_E_NOMEM;
+    const int32_t piece = (int32_t)(STAGE_BYTES / (codes ? 6 : 4) / 64 * 64);
+    const int32_t *const slot = c->run.opt.data() + (size_t)s * c->run.k_run;
+    for (int32_t m0 = 0; m0 < n; m0 += piece) {
+        const int32_t k = std::min(n - m0, piece);
+        int32_t *const v = static_cast<int32_t *>(stage.p);
+        int16_t *const code = codes ? reinterpret_cast<int16_t *>(v + k) : nullptr;
+        stage.idle = false;
+        HIPCHK(rk::launch_read_row(c->dc, c->tb, s, t, c->tiled, m0, k, v, code, c->own_stream));
+        HIPCHK(hipStreamSynchronize(c->own_stream));
+        stage.idle = true;
+        if (c->host[2]) return RK_E_INTERNAL;
+        if (values) std::copy(v, v + k, values + m0);
+        for (int32_t m = 0; codes && m < k; ++m) {  // option slots back to the caller's option indices
+            const int32_t w = code[m], o = w - c->h.L, o3 = o - c->run.k_run;
+            codes[m0 + m] = (int16_t)(o < 0 ? w : o3 < 0 ? c->h.L + slot[o] : c->h.L + c->h.K + slot[o3]);  // o3: case 3
+        }
+    }
+    return RK_OK;
+}
+
+// The schedule of the last solve, which is complete and feasible, into c->schedule.  Its length is
+// known only afterwards: 2 to 7 steps a block are usual, up to 3 L^2 possible; one that does not fit
+// is computed again into a buffer that it fits.
+int build_schedule(rk_chain *c)
+{
+    const int64_t *const res = c->bt_res;
+    Stage stage;
+    for (int32_t turn = 0;; ++turn) {
+        const bool own = c->ops_cap > 0;
+        rk_op *const ops = own ? c->ops : static_cast<rk_op *>(stage.p);
+        const int64_t cap = own ? c->ops_cap : (int64_t)(STAGE_BYTES / sizeof(rk_op));
+        if (!ops) return RK_E_NOMEM;
+        stage.idle = own;
+        HIPCHK(rk::launch_backtrace(c->dc, c->tb, c->M - c->h.x[0], ops, cap, c->bt_res, c->own_stream));
+        HIPCHK(hipStreamSynchronize(c->own_stream));
+        stage.idle = true;
+        if (res[2] != 0 || (turn > 0 && res[0] > cap)) return RK_E_INTERNAL;
+        if (res[0] <= cap) {
+            c->schedule.assign(ops, ops + res[0]);
+            break;
+        }
+        if (c->ops) HIPCHK(hipHostFree(c->ops));
+        c->ops = nullptr;
+        c->ops_cap = 0;
+        if (hipHostMalloc(&c->ops, res[0] * sizeof(rk_op), hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
-            c->rowbuf = nullptr;
+            c->ops = nullptr;
             return RK_E_NOMEM;
         }
-        c->rowbuf_cap = c->W;
+        c->ops_cap = res[0];
     }
-    HIPCHK(rk::launch_read_row(c->dc, c->tb, s, t, c->tiled, c->rowbuf,
-                               codes ? reinterpret_cast<int16_t *>(c->rowbuf + c->W) : nullptr, c->own_stream));
-    HIPCHK(hipStreamSynchronize(c->own_stream));
-    return c->host[2] ? RK_E_INTERNAL : RK_OK;
+    for (rk_op &op : c->schedule)  // option slots back to the caller's option indices
+        if (op.kind == RK_FWD_SAVE || op.kind == RK_BWD || op.kind == RK_REFWD)
+            op.option = c->run.opt[(size_t)op.block * c->run.k_run + op.option];
+    return RK_OK;
 }
 
 }  // namespace
@@ -440,7 +522,6 @@ void rk_chain_destroy(rk_chain *c)
         if (c->own_ws) (void)hipFree(c->own_ws);
         if (c->ops) (void)hipHostFree(c->ops);
         if (c->host) (void)hipHostFree(c->host);
-        if (c->rowbuf) (void)hipHostFree(c->rowbuf);
         if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
         if (c->ev_fill0) (void)hipEventDestroy(c->ev_fill0);
         if (c->ev_fill1) (void)hipEventDestroy(c->ev_fill1);
@@ -550,40 +631,20 @@ int rk_extract_schedule(rk_chain *c, rk_op *ops, int64_t cap, int64_t *n_ops, in
     int rc = answer(c, &ans);
     if (rc != RK_OK) return rc;
     if (ans == RK_INF) return RK_E_INFEASIBLE;
-    // The schedule of this solve is computed once (the two-call protocol asks twice).  Its length
-    // is known only afterwards: 2 to 7 steps a block are usual, up to 3 L^2 possible; one that
-    // does not fit the buffer is computed again into one that it fits.
-    const int64_t *const res = c->bt_res;
-    if (c->bt_fill != c->fills) {
+    if (c->bt_fill != c->fills) {  // computed once per solve (the two-call protocol asks twice)
         c->bt_fill = -1;
-        int64_t want = std::max<int64_t>(c->ops_cap, 8 * (int64_t)c->h.L + 64);
-        for (int32_t turn = 0; turn < 2; ++turn) {
-            if (c->ops_cap < want) {
-                if (c->ops) HIPCHK(hipHostFree(c->ops));
-                c->ops = nullptr;
-                c->ops_cap = 0;
-                if (hipHostMalloc(&c->ops, want * sizeof(rk_op), hipHostMallocDefault) != hipSuccess) {
-                    (void)hipGetLastError();
-                    c->ops = nullptr;
-                    return RK_E_NOMEM;
-                }
-                c->ops_cap = want;
-            }
-            HIPCHK(rk::launch_backtrace(c->dc, c->tb, c->M - c->h.x[0], c->ops, c->ops_cap, c->bt_res, c->own_stream));
-            HIPCHK(hipStreamSynchronize(c->own_stream));
-            if (res[2] != 0 || res[0] <= c->ops_cap) break;
-            want = res[0];
+        try {
+            rc = build_schedule(c);
+        } catch (...) {
+            rc = RK_E_NOMEM;
         }
-        if (res[2] != 0 || res[0] > c->ops_cap) return RK_E_INTERNAL;
+        if (rc != RK_OK) return rc;
         c->bt_fill = c->fills;
     }
-    *n_ops = res[0];
-    if (n_fwd) *n_fwd = res[1];
-    if (!ops || cap < res[0]) return RK_E_BUFSZ;
-    std::copy(c->ops, c->ops + res[0], ops);
-    for (int64_t k = 0; k < res[0]; ++k)  // option slots back to the caller's option indices
-        if (ops[k].kind == RK_FWD_SAVE || ops[k].kind == RK_BWD || ops[k].kind == RK_REFWD)
-            ops[k].option = c->run.opt[(size_t)ops[k].block * c->run.k_run + ops[k].option];
+    *n_ops = (int64_t)c->schedule.size();
+    if (n_fwd) *n_fwd = c->bt_res[1];
+    if (!ops || cap < *n_ops) return RK_E_BUFSZ;
+    std::copy(c->schedule.begin(), c->schedule.end(), ops);
     return RK_OK;
 }
 
@@ -594,18 +655,7 @@ int rk_read_row(rk_chain *c, int32_t s, int32_t t, int32_t *opt_row, int16_t *ar
     DeviceScope ds(c);
     if (!ds.ok) return RK_E_DEVICE;
     HIPCHK(wait_fill(c));
-    int rc = read_row(c, s, t, arg_row != nullptr);
-    if (rc != RK_OK) return rc;
-    if (opt_row) std::copy(c->rowbuf, c->rowbuf + c->W, opt_row);
-    if (arg_row) {
-        const int16_t *const code = reinterpret_cast<const int16_t *>(c->rowbuf + c->W);
-        const int32_t *const slot = c->run.opt.data() + (size_t)s * c->run.k_run;
-        for (int32_t m = 0; m < c->W; ++m) {  // option slots back to the caller's option indices
-            const int32_t v = code[m], o = v - c->h.L, o3 = o - c->run.k_run;
-            arg_row[m] = (int16_t)(o < 0 ? v : o3 < 0 ? c->h.L + slot[o] : c->h.L + c->h.K + slot[o3]);  // o3: case 3
-        }
-    }
-    return RK_OK;
+    return read_row(c, s, t, c->W, opt_row, arg_row);
 }
 
 int rk_tradeoff_curve(rk_chain *c, int32_t *times, int64_t n)
@@ -619,12 +669,7 @@ int rk_tradeoff_curve(rk_chain *c, int32_t *times, int64_t n)
     // budget b leaves b - x_0 slots beyond the chain input: Opt(0, L-1, b - x_0)
     const int64_t x0 = c->h.x[0], lead = std::min<int64_t>(n, x0);
     for (int64_t b = 0; b < lead; ++b) times[b] = RK_INF;
-    if (n > x0) {
-        int rc = read_row(c, 0, c->h.L - 1, false);
-        if (rc != RK_OK) return rc;
-        std::copy(c->rowbuf, c->rowbuf + (n - x0), times + x0);
-    }
-    return RK_OK;
+    return n > x0 ? read_row(c, 0, c->h.L - 1, (int32_t)(n - x0), times + x0, nullptr) : RK_OK;
 }
 
 int rk_last_fill_ms(rk_chain *c, float *ms, int32_t *launches)

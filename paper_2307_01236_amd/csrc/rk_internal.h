@@ -198,10 +198,10 @@ hipError_t launch_fill(const DevChain &ch, const Tables &tb, hipStream_t stream,
                        Profiler *prof);
 // The fill by square tiles (rk_tile.hip); m_ans: the answer's column (-1: none).
 hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hipStream_t stream, int32_t *launches);
-// Row (s, t) as the ABI shows it (codes: choice codes in option slots, or null); values and codes
-// are pinned host memory.  tiled: the table's fill was a tiled one.
-hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool tiled, int32_t *values,
-                           int16_t *codes, hipStream_t stream);
+// Columns m0 .. m0 + n - 1 of row (s, t) as the ABI shows them (codes: choice codes in option slots,
+// or null); values and codes are pinned host memory.  tiled: the table's fill was a tiled one.
+hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool tiled, int32_t m0, int32_t n,
+                           int32_t *values, int16_t *codes, hipStream_t stream);
 // Alg. 3 on the device; ops and res are pinned host memory (ops past cap are counted, not
 // written); res[0] = number of steps, res[1] = index of the first
 // backward, res[2] = status (0 ok, 1 infeasible cell, 2 inconsistent table,

@@ -1357,11 +1357,12 @@ __device__ inline uint64_t sweep_key(const DevChain &ch, const Tables &tb, int32
 // takes 5.8 us.
 constexpr int32_t AR_WAVES = 16;
 __global__ __launch_bounds__(64 * AR_WAVES) void k_read_row(DevChain ch, Tables tb, int32_t s, int32_t t, bool tiled,
-                                                            int32_t *__restrict__ values, int16_t *__restrict__ codes)
+                                                            int32_t m0, int32_t n, int32_t *__restrict__ values,
+                                                            int16_t *__restrict__ codes)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[2] = tiled ? *failed_at(tb) : 0;
     __shared__ uint64_t part[AR_WAVES][64];
-    const int32_t lane = (int32_t)(threadIdx.x & 63), m = (int32_t)blockIdx.x * 64 + lane, mc = min(m, tb.W - 1);
+    const int32_t lane = (int32_t)(threadIdx.x & 63), j = (int32_t)blockIdx.x * 64 + lane, mc = m0 + min(j, n - 1);
     const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
     if (codes) {
         uint64_t best = ~0ull;
@@ -1374,22 +1375,22 @@ __global__ __launch_bounds__(64 * AR_WAVES) void k_read_row(DevChain ch, Tables 
         }
         part[wave][lane] = best;
         __syncthreads();
-        if (wave == 0 && m < tb.W) {
+        if (wave == 0 && j < n) {
             for (int32_t w = 1; w < AR_WAVES; ++w) take(part[w][lane]);
-            codes[m] = best == ~0ull ? (int16_t)-1 : (int16_t)(best & 0xffffu);
+            codes[j] = best == ~0ull ? (int16_t)-1 : (int16_t)(best & 0xffffu);
         }
     }
-    if (wave == 0 && m < tb.W) {
-        const int32_t v = opt_at(tb, ch.L, s, t, m);
-        values[m] = v >= DINF ? RK_INF : v;
+    if (wave == 0 && j < n) {
+        const int32_t v = opt_at(tb, ch.L, s, t, mc);
+        values[j] = v >= DINF ? RK_INF : v;
     }
 }
 
-hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool tiled, int32_t *values,
-                           int16_t *codes, hipStream_t stream)
+hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool tiled, int32_t m0, int32_t n,
+                           int32_t *values, int16_t *codes, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_read_row, dim3((tb.W + 63) / 64), dim3(codes ? 64 * AR_WAVES : 64), 0, stream, ch, tb, s, t,
-                       tiled, values, codes);
+    hipLaunchKernelGGL(k_read_row, dim3((n + 63) / 64), dim3(codes ? 64 * AR_WAVES : 64), 0, stream, ch, tb, s, t, tiled,
+                       m0, n, values, codes);
     return hipGetLastError();
 }
 
