@@ -164,7 +164,49 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     auto at = [](int32_t v, int32_t l) { return __builtin_amdgcn_readlane(v, l); };
 
     // from msa(S0, last end) on, every cell of the tile is lb
-    const bool closed_tile = mb >= ch.msa[row_of(L, S0, min(T0 + TB - 1, L - 1))];
+    const int32_t msa_tile = ch.msa[row_of(L, S0, min(T0 + TB - 1, L - 1))];
+    const bool closed_tile = mb >= msa_tile;
+
+    const int32_t top = DIAG ? lt : TB - 1;  // the wave's last row
+    // the last values of the rows of ap and os (lane: ls), for the summaries
+    int32_t end_a = 0, end_os = 0;
+    auto last = [&](int32_t v, int32_t ls, int32_t &ends) {
+        const int32_t end = __builtin_amdgcn_readlane(v, 63);
+        ends = lane == ls ? end : ends;
+    };
+    auto summarize = [&]() {
+        if (cpe > 0 && (chunk + 1 == n_chunks || (chunk + 1) % cpe == 0) && lane <= top) {
+            const int32_t r = (int32_t)row_of(L, S0 + lane, t), e = 2 * (chunk / cpe);
+            *sum_at(tb, e, r) = end_a;
+            *sum_at(tb, e + 1, r) = end_os;
+        }
+    };
+    auto answer = [&](int32_t v) {
+        if (S0 == 0 && t == L - 1 && m == m_ans) __hip_atomic_store(tb.host, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+
+    // From msa(S0, last end) + reach on, all that the cells read is in closed form, too: the rows are written
+    // as they are, with nothing to wait for (and nobody waits for these columns, see k_tile_init).
+    // Bound by its stores.
+    if (mb - reach >= msa_tile) {
+        if (!real) return;
+        int64_t e = row_of(L, S0 + top, t) * stride + tb.padl + mb + lane;
+        int32_t lb = 0;
+        for (int32_t ls = top; ls >= 0; --ls) {
+            lb = at(r_lb, ls);
+            const bool only1 = (DIAG && ls == lt) || at(r_P1, ls) > 0;  // splits cost at least lb + r(F_s^0)
+            const int32_t a = m >= at(r_need2, ls) ? min(at(r_P, ls) + lb, DINF) : DINF;
+            __builtin_nontemporal_store(only1 ? lb | ONLY_CASE1 : lb, tb.opt + e);
+            __builtin_nontemporal_store(a, tb.ap + e);
+            __builtin_nontemporal_store(lb, tb.os + e);
+            last(a, ls, end_a);
+            end_os = lane == ls ? lb : end_os;
+            e -= (int64_t)(L - (S0 + ls)) * (int32_t)stride;
+        }
+        summarize();
+        answer(lb);
+        return;
+    }
 
     int32_t ost[TB - 1];  // Opt(T0 + 1 + v, t, m - x): right operands inside block T
     if (!DIAG && !closed_tile) {
@@ -337,13 +379,6 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
-    // the last values of the rows of ap and os (lane: ls), for the summaries
-    int32_t end_a = 0, end_os = 0;
-    auto last = [&](int32_t v, int32_t ls, int32_t &ends) {
-        const int32_t end = __builtin_amdgcn_readlane(v, 63);
-        ends = lane == ls ? end : ends;
-    };
-
     // Rows from the last to the first, and one more turn (ls = -1) that only completes the
     // first row's right operand.  The rows are a loop and not unrolled: unrolled, each wave
     // ran 80 KB of code once.  The kernel is bound by the instructions of this loop (16 waves
@@ -352,7 +387,6 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
 #pragma unroll
     for (int32_t u = 0; u < TB; ++u) os[u] = DINF;
     int32_t a_prev = 0, os_prev = 0;  // ap and os values not stored yet
-    const int32_t top = DIAG ? lt : TB - 1;
     // entries of rows (s, t), (s+1, t), (s+2, t) at this wave's first column; row (s-1, t) lies
     // L - s rows before (s, t)
     const int32_t stride32 = (int32_t)stride;
@@ -519,12 +553,8 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         e0 -= (int64_t)(L - s) * stride32;
     }
     __builtin_nontemporal_store(os_prev, tb.os + e1 + lane);  // row S0
-    if (cpe > 0 && (chunk + 1 == n_chunks || (chunk + 1) % cpe == 0) && lane <= top) {
-        const int32_t r = (int32_t)row_of(L, S0 + lane, t), e = 2 * (chunk / cpe);
-        *sum_at(tb, e, r) = end_a;
-        *sum_at(tb, e + 1, r) = end_os;
-    }
-    if (S0 == 0 && t == L - 1 && m == m_ans) __hip_atomic_store(tb.host, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    summarize();
+    answer(best);
 }
 
 hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hipStream_t stream, int32_t *launches)
