@@ -1,12 +1,12 @@
 // rk_tile.hip -- the fill by square tiles of spans.
 //
-// The table's (s, t) triangle is cut into tiles of TB x TB spans: tile (S, T) holds the spans
-// that start in the blocks 16 S .. 16 S + 15 and end in 16 T .. 16 T + 15.  A tile reads only
-// tiles to its left and below (S' >= S, T' <= T), so the tiles of one level T - S are
+// The table's (s, t) triangle is cut into square tiles of up to 16 x 16 spans: tile (S, T) holds
+// the spans that start in block S and end in block T of `side` blocks of the chain each.  A tile
+// reads only tiles to its left and below (S' >= S, T' <= T), so the tiles of one level T - S are
 // independent and the fill is one launch per level, ceil(L / 16) of them, where a launch per
 // span length costs L.  A workgroup owns one tile on 64 budgets (lane = m), one wave per end t:
 //
-//  1. Product: the splits i with both operands in earlier levels (16 S + 16 <= i <= 16 T), a
+//  1. Product: the splits i with both operands in earlier levels (side (S + 1) <= i <= side T), a
 //     plain min-plus matrix product of 16 rows and 16 ends.  Its partial minima stay in LDS.
 //  2. Solve: every wave walks its end t from the tile's last row s up to its first.  Splits
 //     inside block S have their right operand Opt(i, t, m - x_i) among the wave's own earlier
@@ -39,7 +39,7 @@
 
 namespace rk {
 
-constexpr int32_t TB = 16;               // blocks per tile side, waves per workgroup
+constexpr int32_t TB = 16;               // most blocks per tile side, waves per workgroup
 constexpr int32_t TCI = 4;               // splits staged at a time by the product
 constexpr int32_t TOPT = 4;               // options whose words are loaded together
 constexpr int32_t TWIN = 4;              // most 64-column pieces of the case-1 window
@@ -103,11 +103,11 @@ __global__ __launch_bounds__(256) void k_tile_init(Tables tb, const int32_t *msa
     if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[1] = *failed_at(tb) = 0;
 }
 
-// index in LDS of the left operand ap(s, s + u), s = 16 S + ls, u = 0 .. 14 - ls
+// index in LDS of the left operand ap(s, s + u), s = S0 + ls, u = 0 .. 14 - ls
 __device__ constexpr int32_t tri(int32_t ls, int32_t u) { return ls * (TB - 1) - ls * (ls - 1) / 2 + u; }
 
 template <bool DIAG, int NW>
-__global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_t level, int32_t n_chunks,
+__global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_t level, int32_t side, int32_t n_chunks,
                                                   int32_t reach, int32_t cpe, int32_t m_ans)
 {
     __shared__ __align__(16) int32_t cells[TB * TB * 64];  // the product's two staging buffers, then the tile
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
 
     const int32_t L = ch.L, K4 = ch.K4;
     int32_t chunk, sb;
-    chunk_tile(blockIdx.x, (uint32_t)((L + TB - 1) / TB - level), &chunk, &sb);
+    chunk_tile(blockIdx.x, (uint32_t)((L + side - 1) / side - level), &chunk, &sb);
     if (threadIdx.x == 0) {
         int32_t *const started = started_at(tb, sb);
         taken = __hip_atomic_fetch_add(started, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -134,8 +134,9 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     if (chunk >= n_chunks) return;
     const int32_t lane = (int32_t)(threadIdx.x & 63);
     const int32_t lt = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
-    const int32_t S0 = sb * TB, T0 = S0 + level * TB, t = T0 + lt;
-    const bool real = t < L;
+    const int32_t S0 = sb * side, T0 = S0 + level * side, t = T0 + lt;
+    const int32_t t_end = min(T0 + side, L) - 1;  // the tile's last end
+    const bool real = t <= t_end;
     const int32_t mb = chunk * 64, m = mb + lane;
     const int64_t stride = tb.stride;
     const uint32_t col = (uint32_t)(tb.padl + m) * 4u;
@@ -164,10 +165,10 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     auto at = [](int32_t v, int32_t l) { return __builtin_amdgcn_readlane(v, l); };
 
     // from msa(S0, last end) on, every cell of the tile is lb
-    const int32_t msa_tile = ch.msa[row_of(L, S0, min(T0 + TB - 1, L - 1))];
+    const int32_t msa_tile = ch.msa[row_of(L, S0, t_end)];
     const bool closed_tile = mb >= msa_tile;
 
-    const int32_t top = DIAG ? lt : TB - 1;  // the wave's last row
+    const int32_t top = DIAG ? lt : side - 1;  // the wave's last row
     // the last values of the rows of ap and os (lane: ls), for the summaries
     int32_t end_a = 0, end_os = 0;
     auto last = [&](int32_t v, int32_t ls, int32_t &ends) {
@@ -212,7 +213,8 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     if (!DIAG && !closed_tile) {
         const int32_t s = S0 + lt;
         const int32_t *p = tb.ap + row_of(L, s, s) * stride;
-        for (int32_t u = 0; u < TB - 1 - lt; ++u, p += stride) aps[tri(lt, u) * 64 + lane] = ldb(p, col);
+        for (int32_t u = 0; u < side - 1 - lt; ++u, p += stride) aps[tri(lt, u) * 64 + lane] = ldb(p, col);
+        for (int32_t u = max(side - 1 - lt, 0); u < TB - 1 - lt; ++u) aps[tri(lt, u) * 64 + lane] = DINF;
         if (real) {
 #pragma unroll
             for (int32_t v = 0; v < TB - 1; ++v) ost[v] = v < lt ? ldb(tb.os + row_of(L, T0 + 1 + v, t) * stride, col) : DINF;
@@ -223,7 +225,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         // ub, the least of its candidates at the last budget of the chunks before, and a split
         // whose candidate at this group of chunks' last budget is no lower than ub in any of
         // the tile's cells can be left out, once the accumulators start from ub.
-        const int32_t i0 = S0 + TB, n_all = T0 - i0 + 1;
+        const int32_t i0 = S0 + side, n_all = T0 - i0 + 1;
         const int32_t grp_e = 2 * (chunk / max(cpe, 1));  // the summaries' entry
         int32_t n_list = n_all;
         const bool listed = cpe > 0 && n_all >= TLIST_MIN;
@@ -231,7 +233,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
             // TPIECE splits at a time through LDS, one cell and every fourth split per thread
             const int32_t cell = (int32_t)(threadIdx.x & 255), grp = lt >> 2, cr = cell >> 4, ck = cell & 15;
             i32x2 *const sa = (i32x2 *)cells, *const sbv = sa + TPIECE * (TB + 1);
-            const int32_t ra = (int32_t)row_of(L, S0 + lt, i0 - 1), rb = min(T0 + (lane & 15), L - 1);
+            const int32_t ra = (int32_t)row_of(L, S0 + min(lt, side - 1), i0 - 1), rb = min(T0 + (lane & 15), t_end);
             // the entry before this group's and this group's
             auto both = [&](int32_t e, int32_t r) -> i32x2 {
                 return i32x2{e > 1 ? *sum_at(tb, e - 2, r) : DINF, *sum_at(tb, e, r)};
@@ -303,16 +305,17 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
             for (int32_t k = 0; k < 4; ++k) acc[r][k] = listed ? ubs[(4 * wr + r) * TB + 4 * wc + k] : DINF;
         if (listed) n_list = __builtin_amdgcn_readfirstlane(n_kept);
         __syncthreads();
-        const int32_t *const pa = tb.ap + row_of(L, S0 + 4 * wc, i0 - 1) * stride;
-        const int32_t *const pb = tb.os + min(T0 + 4 * wc, L - 1) * stride;
+        // (rows and ends past the tile's last: the last again)
+        const int32_t *const pa = tb.ap + row_of(L, min(S0 + 4 * wc, i0 - 1), i0 - 1) * stride;
+        const int32_t *const pb = tb.os + min(T0 + 4 * wc, t_end) * stride;
         uint32_t ca[4], cb[4];  // byte offsets of the four rows from the first
         {
             uint32_t ra = 0;
 #pragma unroll
             for (int32_t r = 0; r < 4; ++r) {
                 ca[r] = ra * (uint32_t)pitch + col;
-                cb[r] = (uint32_t)max(min(r, L - 1 - (T0 + 4 * wc)), 0) * (uint32_t)pitch + col;
-                ra += (uint32_t)(L - 1 - (S0 + 4 * wc + r));
+                cb[r] = (uint32_t)max(min(r, t_end - (T0 + 4 * wc)), 0) * (uint32_t)pitch + col;
+                if (S0 + 4 * wc + r < i0 - 1) ra += (uint32_t)(L - 1 - (S0 + 4 * wc + r));
             }
         }
         i32x4 qa[2], qb[2];
@@ -403,7 +406,7 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     }
     int32_t best = DINF;
     for (int32_t ls = top; ls >= -1; --ls) {
-        const int32_t s = S0 + ls, n_in = DIAG ? lt - ls : TB - 1 - ls;  // splits s+1 .. s+n_in inside block S
+        const int32_t s = S0 + ls, n_in = top - ls;  // splits s+1 .. s+n_in inside block S
         const bool rest = !DIAG || n_in > 0;  // row (s+1, t) exists
         const bool need_os = n_in > 0;        // ... and is one of this wave's
         const int32_t lsc = max(ls, 0);
@@ -559,13 +562,16 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
 
 hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hipStream_t stream, int32_t *launches)
 {
-    const int32_t nb = (ch.L + TB - 1) / TB, n_chunks = (tb.W + 63) / 64;
+    // Tiles of equal sides, the fewest that hold L blocks: 17 blocks are two of 9, not 16 and 1 (a
+    // workgroup takes as long for one end as for 16, and a tile's rows follow one another).
+    const int32_t side = (ch.L + (ch.L + TB - 1) / TB - 1) / ((ch.L + TB - 1) / TB);
+    const int32_t nb = (ch.L + side - 1) / side, n_chunks = (tb.W + 63) / 64;
     // Case 1 reads its row at K shifts.  Staged in LDS that costs a load per 64 columns of reach
     // and cell, unstaged one per option (and one for the right operand): staged where it fits.
     const int32_t nw = ch.reach <= 64 * (TWIN - 1) ? 1 + (ch.reach + 63) / 64 : 0;
     // chunks per entry of the summaries (0: no pads to keep them in)
     const int32_t cpe = tb.padl >= 64 ? (n_chunks + SUM_GROUPS - 1) / SUM_GROUPS : 0;
-    using Kernel = void (*)(DevChain, Tables, int32_t, int32_t, int32_t, int32_t, int32_t);
+    using Kernel = void (*)(DevChain, Tables, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t);
     static const Kernel kernels[2][TWIN + 1] = {
         {k_tile<false, 0>, k_tile<false, 1>, k_tile<false, 2>, k_tile<false, 3>, k_tile<false, 4>},
         {k_tile<true, 0>, k_tile<true, 1>, k_tile<true, 2>, k_tile<true, 3>, k_tile<true, 4>}};
@@ -575,8 +581,8 @@ hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hip
     if (e != hipSuccess) return e;
     for (int32_t level = 0; level < nb; ++level) {
         const dim3 grid(chunk_grid(n_chunks, nb - level));
-        hipLaunchKernelGGL(kernels[level == 0][nw], grid, dim3(TB * 64), 0, stream, ch, tb, level, n_chunks, ch.reach,
-                           cpe, m_ans);
+        hipLaunchKernelGGL(kernels[level == 0][nw], grid, dim3(TB * 64), 0, stream, ch, tb, level, side, n_chunks,
+                           ch.reach, cpe, m_ans);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     *launches = nb + 1;

@@ -22,6 +22,16 @@ def test_tile_and_chunk_edges(L, M):
     full_parity(ch, M)
 
 
+@pytest.mark.parametrize("L", [18, 19, 20, 23, 27, 30, 34, 37, 41, 44, 50, 53, 61, 65, 66, 97, 129, 170])
+def test_tile_sides(L):
+    """Chains cut into equal tiles of 9 to 16 blocks, the last one smaller or not; windows of LDS and
+    none, and from 97 blocks on products of 40 splits and more."""
+    M = 150 if L < 100 else 90
+    for seed, xmax, amax in ((0, 5, 9), (1, 80, 160)):
+        full_parity(make_random_chain(1300 + 2 * L + seed, L, 1 + L % 4, allow_zero=L % 2 == 0, xmax=xmax if L < 100 else 3,
+                                      amax=amax if L < 100 else 5, tmax=4, tmin=0, small_times=L % 3 == 0), M + 250 * seed)
+
+
 @pytest.mark.parametrize("reach", [0, 1, 63, 64, 65, 128, 129, 192, 193])
 def test_reach_of_case_1(reach):
     """The largest x + mem of an option decides how many columns left of a chunk are staged."""
