@@ -50,6 +50,7 @@ struct rk_chain {
     const int32_t *g_tables = nullptr;
     hipStream_t g_stream = nullptr;
     bool g_prof = false;
+    int32_t g_launches = 0;
 
     std::vector<rk_op> schedule;  // of the solve number bt_fill
     int64_t fills = 0;            // solves queued so far
@@ -320,8 +321,8 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
         HIPCHK(hipMalloc(&c->prof.d_ctr, rk::CTR_WORDS * sizeof(unsigned long long)));
     c->tb.ctr = c->prof.count ? c->prof.d_ctr : nullptr;
     c->tb.host = c->host;
-    // the saving sweep and profiled fills run by levels of diagonals
-    c->tiled = !c->dc.c3 && !c->prof.on;
+    // the saving sweep, profiled fills and some very wide ones run by levels of diagonals
+    c->tiled = !c->dc.c3 && !c->prof.on && rk::tiles_pay(c->dc, g.W);
     auto launch = [&]() {
         return c->tiled ? rk::launch_tiles(c->dc, c->tb, M - c->h.x[0], stream, &c->launches)
                         : rk::launch_fill(c->dc, c->tb, stream, &c->launches, &c->prof);
@@ -343,6 +344,7 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
         HIPCHK(launch());
     } else if (replay) {
         HIPCHK(hipGraphLaunch(c->gexec, stream));
+        c->launches = c->g_launches;
     } else {
         if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
         c->gexec = nullptr;
@@ -365,6 +367,7 @@ int fill(rk_chain *c, int32_t M, const Geometry &g, int32_t *tables, hipStream_t
                 c->g_tables = tables;
                 c->g_stream = stream;
                 c->g_prof = c->prof.on;
+                c->g_launches = c->launches;
             }
             if (graph) (void)hipGraphDestroy(graph);
             (void)hipGetLastError();

@@ -196,7 +196,9 @@ extern const char *const kFillKernelNames[KFILL_NKINDS];
 // Launchers (rk_kernels.hip).  All return hipError_t of the launch.
 hipError_t launch_fill(const DevChain &ch, const Tables &tb, hipStream_t stream, int32_t *launches,
                        Profiler *prof);
-// The fill by square tiles (rk_tile.hip); m_ans: the answer's column (-1: none).
+// The fill by square tiles (rk_tile.hip); m_ans: the answer's column (-1: none).  tiles_pay: whether it
+// is the faster one for W columns.
+bool tiles_pay(const DevChain &ch, int32_t W);
 hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hipStream_t stream, int32_t *launches);
 // Columns m0 .. m0 + n - 1 of row (s, t) as the ABI shows them (codes: choice codes in option slots,
 // or null); values and codes are pinned host memory.  tiled: the table's fill was a tiled one.

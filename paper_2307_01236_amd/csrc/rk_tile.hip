@@ -560,11 +560,32 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     answer(best);
 }
 
+// Tiles of equal sides, the fewest that hold L blocks: 17 blocks are two of 9, not 16 and 1 (a
+// workgroup takes as long for one end as for 16, and a tile's rows follow one another).
+static int32_t tile_side(int32_t L)
+{
+    const int32_t nb = (L + TB - 1) / TB;
+    return (L + nb - 1) / nb;
+}
+
+// Two tiles of 9-12 blocks leave a third of the waves idle, which shows where the budgets are so many that
+// neither launches nor the schedule (faster with this fill's marks) count.  Fill by diagonals -> by
+// tiles, shifts of up to a few thousand columns, 1 to 20 options: 17 blocks x 50001 budgets 154-255 ->
+// 181-249 us, x 100001 233-378 -> 305-428 us, x 300001 0.54-0.87 -> 0.81-1.15 ms; 20 x 100001 295-477 -> 349-493
+// us, x 300001 0.70-1.11 -> 0.93-1.32 ms; 24 x 100001 391-675 -> 421-654 us, x 300001 0.99-1.71 -> 1.14-1.78 ms;
+// 26 blocks and more: tiles as fast or faster, but for single options (at 33 x 300001 2.20 -> 2.49 ms).
+// Columns past storing everything don't count, tiles write them faster (24 x 200001, small shifts: 333 -> 178 us).
+bool tiles_pay(const DevChain &ch, int32_t W)
+{
+    const int32_t side = tile_side(ch.L);
+    if (ch.L <= TB || ch.L > 2 * TB || side > 12) return true;
+    const int64_t open = (int64_t)ch.h_msa[row_of(ch.L, 0, ch.L - 1)] + ch.reach;
+    return std::min<int64_t>(W, open) < 50000 * (side - 7);
+}
+
 hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hipStream_t stream, int32_t *launches)
 {
-    // Tiles of equal sides, the fewest that hold L blocks: 17 blocks are two of 9, not 16 and 1 (a
-    // workgroup takes as long for one end as for 16, and a tile's rows follow one another).
-    const int32_t side = (ch.L + (ch.L + TB - 1) / TB - 1) / ((ch.L + TB - 1) / TB);
+    const int32_t side = tile_side(ch.L);
     const int32_t nb = (ch.L + side - 1) / side, n_chunks = (tb.W + 63) / 64;
     // Case 1 reads its row at K shifts.  Staged in LDS that costs a load per 64 columns of reach
     // and cell, unstaged one per option (and one for the right operand): staged where it fits.

@@ -223,3 +223,32 @@ def test_failure_belongs_to_the_table_it_happened_in():
         assert int(last[256]) == 0
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("L,first", [(17, 100000), (20, 150000), (24, 250000)])
+def test_very_wide_budgets_by_diagonals(L, first):
+    """17-24 blocks: from `first` columns on (as far as storing everything does not fit) the fill runs by
+    diagonals, replayed from a captured graph; both sides of the line, and back, in one chain."""
+    ch = make_random_chain(1700 + L, L, 2, xmax=2 * first // L, amax=8 * first // L, tmax=first // L, tmin=0)
+    xbar = ch.x[1:, None].astype(np.int64) + ch.mem
+    need, cost = xbar + np.maximum(ch.tmp_fwd, ch.tmp_bwd), ch.fwd + ch.bwd
+    fits = 0  # the smallest budget in which the cheapest options of all blocks fit
+    for i in range(L - 1, -1, -1):
+        cheap = cost[i] == cost[i].min()
+        fits = min(max(int(n), int(x) + fits if i < L - 1 else 0) for n, x in zip(need[i][cheap], xbar[i][cheap]))
+    assert fits > first
+    s = rk.Solver(ch)
+    try:
+        for M in (first - 1, first - 2, first - 1, first - 1):  # M + 1 columns
+            sol = oracle.solve(ch, M)
+            assert s.solve(M) == sol.answer
+            assert (s.fill_ms()[1] == 3) == (M + 1 < first)
+            assert np.array_equal(s.tradeoff_curve(), oracle.tradeoff_curve(sol))
+            for i, j in ((0, L - 1), (0, L // 2), (L // 2, L - 1), (3, 4)):
+                for x, y in zip(s.row(i, j), (sol.opt_row(i, j), sol.arg_row(i, j))):
+                    assert np.array_equal(x, y), (i, j)
+            ops, nf = s.schedule()
+            exp = oracle.schedule(sol, M)
+            assert np.array_equal(ops, exp[0]) and nf == exp[1]
+    finally:
+        s.close()
