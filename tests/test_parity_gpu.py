@@ -24,16 +24,19 @@ def say(*a):
     sys.stdout.flush()
 
 
-def full_parity(ch, M=None, check_schedule=True, prune=True):
-    """Whole Opt and choice tables, the answer and the schedule."""
+def full_parity(ch, M=None, check_schedule=True, prune=True, diagonals=False):
+    """Whole Opt and choice tables, the answer and the schedule.  diagonals: of the fill by levels of
+    diagonals (that of profiled solves) where the chain would be filled by tiles."""
     M = ch.M if M is None else M
-    say(f"  full parity {ch.name} L={ch.L} K={ch.K} M={M} pruning={prune}")
+    say(f"  full parity {ch.name} L={ch.L} K={ch.K} M={M} pruning={prune} diagonals={diagonals}")
     sol = oracle.solve(ch, M)
     s = rk.Solver(ch)
     try:
         s.set_option_pruning(prune)
+        s.set_profiling(diagonals)
         ans = s.solve(M)
         assert ans == sol.answer, (ans, sol.answer)
+        assert not diagonals or sum(v[0] for v in s.kernel_stats().values()) >= ch.L
         g_opt, g_arg = s.rows()
         o_opt, o_arg = sol.rows()
         bad = np.argwhere(g_opt != o_opt)
@@ -96,8 +99,9 @@ def test_fuzz_full_tables(idx):
 
 @pytest.mark.parametrize("idx", range(4))
 def test_longer_random_chains_full_tables(idx):
-    """Random (not uniform) chains long enough for band products at spans 32, 64 and 96 and
-    for both mid-product levels, including the folds into stored partials (lo > 0)."""
+    """Random (not uniform) chains of 65-100 blocks; by diagonals (test_diagonals_gpu.py) long enough
+    for band products at spans 32, 64 and 96 and for both mid-product levels, including the folds into
+    stored partials (lo > 0)."""
     rng = np.random.default_rng(777 + idx)
     L = int(rng.integers(65, 101))
     K = int(rng.integers(1, 17))
@@ -332,8 +336,9 @@ def test_profiling_device_counts(cfg):
 
 
 def test_graph_replays_match_oracle():
-    """Repeated solves at one budget replay the captured launch sequence; each replay, with
-    other solves and read-backs in between, must still match the oracle exactly."""
+    """Repeated solves at one budget, by tiles and (profiled) by diagonals in turn, with other solves and
+    read-backs in between, match the oracle exactly.  (Replays of the library's captured graph:
+    test_sweep_gpu.py, and test_tiles_gpu.py for very wide budgets.)"""
     ch, other = make_config_chain(1), make_config_chain(0)
     sol, osol = oracle.solve(ch), oracle.solve(other)
     o_opt, o_arg = sol.rows()
@@ -350,7 +355,7 @@ def test_graph_replays_match_oracle():
             ops, nfwd = s.schedule()
             assert np.array_equal(ops, exp_ops[0]) and nfwd == exp_ops[1]
             assert t.solve() == osol.answer
-            s.set_profiling(rep % 2 == 1)  # switching profiling re-captures the sequence
+            s.set_profiling(rep % 2 == 1)  # the next solve by diagonals
     finally:
         s.close()
         t.close()
@@ -425,8 +430,8 @@ def test_grid_options_pruned_and_unpruned(prune):
 
 
 def test_pruning_switch_between_solves():
-    """Turning pruning off and on between solves of one chain rebuilds the device arrays and
-    the captured launch sequence; every solve still matches the oracle."""
+    """Turning pruning off and on between solves of one chain rebuilds the device arrays;
+    every solve still matches the oracle."""
     ch = make_grid_chain(6, 20, 8, 8)
     sol = oracle.solve(ch)
     o_opt, o_arg = sol.rows()
@@ -455,8 +460,8 @@ def test_backtrace_with_option_sizes_in_global_memory():
 
 
 def test_longest_chain():
-    """RK_MAX_L = 2000 blocks (1999 finalize launches; a backtrace whose LDS stack of up to
-    2L + 8 frames and x copy take 72 KB).  Exact parity on sub-chains at both ends; the
+    """RK_MAX_L = 2000 blocks (125 levels of tiles; a backtrace whose LDS stack of up to 2L + 8
+    frames, window and copies of x, P and lb take 120 KB).  Exact parity on sub-chains at both ends; the
     schedule replays legally in the oracle's simulator at exactly the answer and within the
     budget (the oracle's full table would take minutes; the simulator shares nothing with it)."""
     L = rk.RK_MAX_L
@@ -523,8 +528,8 @@ def test_fill_inside_a_torch_graph_capture():
 
 
 def test_option_sizes_beyond_the_staged_halo():
-    """Options that keep up to 700 slots: case 1's shift exceeds the 256 columns the finalize
-    stages in LDS, so it reads the shifted row from global memory.  Full-table parity."""
+    """Options that keep up to 700 slots: case 1's shift exceeds the columns that tiles (192) and the
+    finalize (256) stage in LDS, so the shifted row is read from global memory.  Full-table parity."""
     ch = make_random_chain(4242, 40, 4, xmax=40, amax=700, tmax=60, tmin=0)
     assert int(ch.mem.max()) + int(ch.x.max()) > 256
     full_parity(ch, 3000)
@@ -532,7 +537,7 @@ def test_option_sizes_beyond_the_staged_halo():
 
 @pytest.mark.parametrize("idx", range(8))
 def test_medium_random_chains_sampled(idx):
-    """Random chains of 110-260 blocks (several bands, ragged band and column tails), 1-24
+    """Random chains of 110-260 blocks (ragged tiles and column tails), 1-24
     options, budgets 300-2500: exact parity on three sampled sub-chains, and on the whole
     table the infeasibility pattern, monotonicity in m and a schedule that replays at the
     answer."""
@@ -570,8 +575,8 @@ def test_medium_random_chains_sampled(idx):
 @pytest.mark.parametrize("M", [24998, 25000])
 def test_mid_levels_at_large_budgets(M):
     """64 blocks at about 25 000 budget columns (1.6e6 blocks x budget columns) with shifts of
-    up to 50 columns: mid products of widths 16 and 8 and a finalize that covers the splits
-    whose longer operand spans the last 8 spans.  Full-table parity."""
+    up to 50 columns.  Full-table parity by tiles; by diagonals (test_diagonals_gpu.py too) mid products
+    of widths 16 and 8 and a finalize that covers the splits whose longer operand spans the last 8 spans."""
     ch = make_random_chain(6464, 64, 3, xmax=50, amax=400, tmax=100, tmin=0)
     sol = full_parity(ch, M)
     assert sol.answer != INF
@@ -592,8 +597,8 @@ def test_mid_levels_at_large_budgets(M):
 @pytest.mark.parametrize("seed", [97003, 97008])
 def test_several_bands_at_large_tables(seed):
     """Chains of 64-110 blocks with at least 1.6e6 blocks x budget columns (78 and 105
-    blocks, one option): two or three band products, mids of widths 16 and 8, and shifts
-    of up to a few hundred columns.  Full-table parity."""
+    blocks, one option) and shifts of up to a few hundred columns; by diagonals
+    (test_diagonals_gpu.py) two or three band products and mids of widths 16 and 8.  Full-table parity."""
     rng = np.random.default_rng(seed)
     L = int(rng.integers(64, 110))
     K = int(rng.integers(1, 4))
@@ -607,7 +612,6 @@ def test_several_bands_at_large_tables(seed):
 
 def test_wide_budget():
     """200 001 budget columns on a short chain with large sizes: a left pad of ~2000 columns,
-    1 563 column chunks per cell in the finalize and shifts far beyond its staged halo.
-    Full-table parity."""
+    3 126 column chunks of one tile and shifts far beyond those staged.  Full-table parity."""
     ch = make_random_chain(777, 12, 3, xmax=2000, amax=9000, tmax=3000, tmin=0)
     full_parity(ch, 200000)

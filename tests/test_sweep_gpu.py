@@ -131,3 +131,36 @@ def test_schedule_search_edges(L, K):
             check_same_schedule(s, sol, ch, M)
         finally:
             s.close()
+
+
+def test_graph_replays_match_oracle():
+    """Repeated solves at one budget replay the library's captured graph: with other solves and
+    read-backs in between, the tables overwritten, another budget and back, with profiled solves (no
+    graph) among them, each solve still matches the oracle."""
+    import torch
+    ch, other = with_refwd(make_config_chain(1), 5, 0.0, 0.4), make_config_chain(0)
+    st = torch.cuda.Stream()
+    budgets = (300, 300, 300, 140, 300, 300)
+    sols = {M: oracle.solve(ch, M) for M in set(budgets)}
+    s, t = rk.Solver(ch), rk.Solver(other)
+    try:
+        n = s.workspace_bytes(max(budgets))
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        launches = set()
+        for k, M in enumerate(budgets):
+            say(f"  solve {k} at {M}")
+            s.set_profiling(k == 4)
+            ws.zero_()
+            torch.cuda.synchronize()
+            s.solve_async(M, ws.data_ptr(), n, st.cuda_stream)
+            assert s.result() == sols[M].answer
+            launches.add(s.fill_ms()[1])
+            g_opt, g_arg = s.rows()
+            o_opt, o_arg = sols[M].rows()
+            assert np.array_equal(g_opt, o_opt) and np.array_equal(g_arg, o_arg), k
+            check_same_schedule(s, sols[M], ch, M)
+            assert t.solve() == oracle.solve(other).answer
+        assert len(launches) <= 2 and min(launches) >= ch.L
+    finally:
+        s.close()
+        t.close()

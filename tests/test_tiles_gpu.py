@@ -139,13 +139,16 @@ def test_two_chains_at_once_on_two_streams():
 
 def test_many_workgroups_of_two_fills_at_once():
     """Two fills of more workgroups per launch than the chip holds, on two streams: each waits
-    only for workgroups of its own that have started."""
+    only for workgroups of its own that have started.  The fill by diagonals on the other side."""
     import torch
     ch = make_random_chain(77, 128, 3, M=9000, xmax=60, amax=300, tmax=9)
     solvers = [rk.Solver(ch) for _ in range(2)]
     try:
+        solvers[0].set_profiling(1)  # the fill by levels of diagonals
         want = solvers[0].solve()
         curve = solvers[0].tradeoff_curve()
+        rows = {(i, j): solvers[0].row(i, j) for i, j in ((0, 127), (0, 63), (40, 127), (31, 80))}
+        solvers[0].set_profiling(0)
         n = solvers[0].workspace_bytes(ch.M)
         ws = [torch.empty(n, dtype=torch.uint8, device="cuda:0") for _ in solvers]
         st = [torch.cuda.Stream() for _ in solvers]
@@ -156,6 +159,9 @@ def test_many_workgroups_of_two_fills_at_once():
             for s in solvers:
                 assert s.result() == want
                 assert np.array_equal(s.tradeoff_curve(), curve)
+                for (i, j), (opt, arg) in rows.items():
+                    g_opt, g_arg = s.row(i, j)
+                    assert np.array_equal(g_opt, opt) and np.array_equal(g_arg, arg), (i, j)
     finally:
         for s in solvers:
             s.close()
