@@ -131,11 +131,12 @@ int rk_solve(rk_chain *c, int32_t M, int32_t *opt_out);
  * Same fill, asynchronous, in caller memory: d_workspace is device memory of
  * at least rk_workspace_bytes(c, M) bytes (for instance a torch tensor) and
  * stream a hipStream_t (NULL: a stream the chain owns).  Returns once the work
- * is queued.  With the saving sweep the fill's kernel sequence is captured into a HIP graph on
- * first use and replayed while M, the workspace, the stream and the profiling switch
- * stay the same; without it the fill's few launches go straight to the stream.  The workspace must stay allocated and untouched until the
- * chain is destroyed or solved again; the chain reads results from it.  Call
- * rk_result to wait and read the answer.
+ * is queued.  A fill by levels of diagonals (with the saving sweep; and 17-24 blocks at a
+ * hundred thousand budgets and more) is captured into a HIP graph on first use and replayed
+ * while M, the workspace, the stream and the profiling switch stay the same; the few launches
+ * of any other fill go straight to the stream.  The workspace must stay allocated and
+ * untouched until the chain is destroyed or solved again; the chain reads results from it.
+ * Call rk_result to wait and read the answer.
  *
  * On a stream the caller is capturing into a HIP graph, the kernels are launched
  * directly and become part of the caller's graph; nothing is allocated, uploaded or
@@ -216,8 +217,9 @@ int rk_last_fill_ms(rk_chain *c, float *ms, int32_t *launches);
 /*
  * Kernel-level timing (for benchmarks; mode 0, off, by default).  In mode 1 or 2 the
  * fill runs by levels of diagonals (band products, mid products and a finalize per span
- * length: how chains with the saving sweep are always filled; other chains are otherwise
- * filled by square tiles of spans, one kernel per level), launches its kernels one by one
+ * length: how chains with the saving sweep are always filled; most other chains are
+ * filled by square tiles of spans otherwise, one kernel per level, which are not counted or
+ * timed one by one: rk_last_fill_ms has their time), launches its kernels one by one
  * instead of replaying a graph, and the runtime
  * records a pair of HIP events with every dispatch, at the kernel's start and end
  * (hipExtLaunchKernelGGL), so a launch's time is the kernel's own.  Mode 2 also runs

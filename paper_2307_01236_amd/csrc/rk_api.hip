@@ -3,7 +3,7 @@
 // Host side: argument checks, the per-chain precompute of App. C's derived
 // quantities, device buffers, kernel launches and read-back.  No step of the
 // dynamic program itself runs here; the fill, the choice recovery and Alg. 3
-// all run in the kernels of rk_kernels.hip.
+// all run in the kernels of rk_tile.hip and rk_kernels.hip.
 #include <algorithm>
 #include <mutex>
 #include <new>
@@ -24,7 +24,7 @@ struct rk_chain {
     rk::RunSlots run;
 
     int device = -1;
-    void *d_chain = nullptr;  // x | xbar | c1 | need1 | need1max | P | need2 | lb (options: run slots)
+    void *d_chain = nullptr;  // every device array of dc (options: run slots)
     DevChain dc{};
 
     void *own_ws = nullptr;  // tables owned by the chain (rk_solve)
@@ -42,8 +42,8 @@ struct rk_chain {
     int32_t launches = 0;
     rk::Profiler prof;
 
-    // The fill's launch sequence is captured once into a HIP graph and replayed while the
-    // budget, the tables, the stream and the profiling switch stay the same.
+    // The launch sequence of a fill by diagonals is captured once into a HIP graph and replayed while
+    // the budget, the tables, the stream and the profiling switch stay the same.
     hipStream_t own_stream = nullptr;  // used when the caller passes no stream
     hipGraphExec_t gexec = nullptr;
     int32_t g_M = -1;

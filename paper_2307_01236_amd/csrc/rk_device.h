@@ -1,8 +1,6 @@
 // rk_device.h -- device helpers shared by the fill kernels.
 #pragma once
 
-#include <type_traits>
-
 #include "rk_internal.h"
 
 namespace rk {
@@ -30,40 +28,10 @@ static inline uint32_t chunk_grid(int32_t n_chunks, int32_t n_idx)
     return (uint32_t)(8 * ((n_chunks + 7) / 8) * n_idx);
 }
 
-// Maximum of a 32-bit value over the 64 lanes of a wavefront (all lanes active): DPP
-// exchanges inside each row of 16 lanes, then the four row maxima read as scalars.
-__device__ inline uint32_t wave_max_u32(uint32_t v)
-{
-    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, false));   // quad_perm 1,0,3,2
-    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, false));   // quad_perm 2,3,0,1
-    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, false));  // row_ror 4
-    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, false));  // row_ror 8
-    const uint32_t r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
-    const uint32_t r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
-    return max(max(r0, r1), max(r2, r3));
-}
-
-// Calls f(integral_constant<int, U>) for U = B .. E-1 in order: a loop unrolled by
-// construction, whose index is a compile-time constant in the body.
-template <int B, int E, typename F>
-__device__ inline void static_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
 // load at a byte offset from a wave-uniform base (one scalar base + one 32-bit lane offset)
 __device__ inline int32_t ldb(const int32_t *base, uint32_t byte_off)
 {
     return *(const int32_t *)((const char *)base + byte_off);
 }
-
-// A store marked nontemporal: its line is the first the caches let go.  The finalize writes
-// several rows per cell that only later launches read, most of them on other XCDs; with
-// these stores so marked the fill measured 0.13 ms faster (0.33 ms with the saving sweep),
-// the products and mids included, which keep more of their operands in L2.
-__device__ inline void st_nt(int32_t v, int32_t *p) { __builtin_nontemporal_store(v, p); }
 
 }  // namespace rk

@@ -11,6 +11,12 @@
 // columns m = 0..M, then padding to a multiple of 64 (256 B) so every row
 // starts 256-byte aligned.
 //
+// That pads and the extra row hold infinity is true of the fill by diagonals, whose
+// kernels (and the backtrace of the saving sweep, which it always fills) read them.  The
+// fill by tiles reads neither, leaves the extra row as it is, and keeps its own words there:
+// summaries of rows in the left pads of opt, ap and os (rk_tile.hip), its counters and the
+// mark of a failed fill in the slack rows before row 0 of opt.
+//
 //   opt  Opt(s,t,m) at opt[row(s,t)*stride + padl + m].  The left pad lets a
 //        read at m - xbar (case 1) run unmasked: columns below 0 read
 //        infinity.  Before a span is final its slot holds the partial minimum

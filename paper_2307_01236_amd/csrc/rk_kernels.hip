@@ -12,11 +12,16 @@
 // time and validity folded in.  Which choice realises a minimum is recomputed from
 // the finished table where it is needed (Alg. 3 does the same: it asks which case
 // attains Opt(s,t,m)), so the fill keeps no argmin bookkeeping.
+//
+// This file holds the fill by levels of diagonals (chains with the saving sweep, profiled solves,
+// some chains of two tiles at very many budgets), the reading of rows and Alg. 3; the fill by tiles
+// of all other chains is in rk_tile.hip.
 #include "rk_device.h"
 
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rk {
 
@@ -135,6 +140,19 @@ constexpr uint32_t OOB = 0x80000000u;
 // them stay inside the table with its slack rows.
 // ---------------------------------------------------------------------------------------
 __device__ inline uint32_t sat_add(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+
+// Maximum of a 32-bit value over the 64 lanes of a wavefront (all lanes active): DPP
+// exchanges inside each row of 16 lanes, then the four row maxima read as scalars.
+__device__ inline uint32_t wave_max_u32(uint32_t v)
+{
+    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, false));   // quad_perm 1,0,3,2
+    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, false));   // quad_perm 2,3,0,1
+    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, false));  // row_ror 4
+    v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, false));  // row_ror 8
+    const uint32_t r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
+    const uint32_t r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
+    return max(max(r0, r1), max(r2, r3));
+}
 
 // Splits of the band product's first pass, before it cuts its split range (see k_product).
 constexpr int32_t PROD_PREFIX = 40;
@@ -453,6 +471,17 @@ __global__ __launch_bounds__(NW * 64) void k_product(DevChain ch, Tables tb, int
 // loads are issued one split ahead of its relaxation.  Cells past the table are computed
 // and not stored (their operand rows are clamped into the table).
 // ---------------------------------------------------------------------------------------
+// Calls f(integral_constant<int, U>) for U = B .. E-1 in order: a loop unrolled by
+// construction, whose index is a compile-time constant in the body.
+template <int B, int E, typename F>
+__device__ inline void static_for(F &&f)
+{
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
+    }
+}
+
 // rows (group A) or ends (group B) of a mid product tile
 template <int WD>
 constexpr int mid_rows() { return 4; }
@@ -736,6 +765,12 @@ __device__ inline int32_t ldrow(const int32_t *base, uint32_t pitch, uint32_t by
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, (int)pitch, 0x00020000);
     return __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, 0);
 }
+
+// A store marked nontemporal: its line is the first the caches let go.  The finalize writes
+// several rows per cell that only later launches read, most of them on other XCDs; with
+// these stores so marked the fill measured 0.13 ms faster (0.33 ms with the saving sweep),
+// the products and mids included, which keep more of their operands in L2.
+__device__ inline void st_nt(int32_t v, int32_t *p) { __builtin_nontemporal_store(v, p); }
 
 // The arguments before the first aggregate are preloaded into SGPRs when a wave starts (the
 // library is built with kernarg preloading of up to 14 dwords): the three table pointers and

@@ -22,9 +22,9 @@
 // another workgroup's load 0.35-0.5 us later, on one XCD or across).
 //
 // Measured against one launch per diagonal (4.5-10 us each, mostly latency), fill time at blocks
-// x budgets x options: 8 x 501 x 3 42 -> 20 us, 64 x 1001 x 5 416 -> 159 us, 128 x 2001 x 8
-// 1.08 -> 0.42 ms, 256 x 4001 x 8 3.51 -> 2.03 ms, 384 x 6001 x 16 8.2 -> 5.9 ms, 1000 x 601 x 4
-// 24.7 -> 16.9 ms.
+// x budgets x options: 8 x 501 x 3 42 -> 20 us, 64 x 1001 x 5 416 -> 165 us, 128 x 2001 x 8
+// 1.08 -> 0.43 ms, 256 x 4001 x 8 3.51 -> 2.02 ms, 384 x 6001 x 16 8.2 -> 5.9 ms, 1000 x 601 x 4
+// 24.7 -> 15.9 ms.
 //
 // Waits end: a workgroup waits only for columns to the left of its own in the same tile, and
 // which columns it takes is decided when it starts: the tile's next ones, by a counter per
@@ -36,6 +36,7 @@
 #include "rk_device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rk {
 
@@ -188,7 +189,8 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
 
     // From msa(S0, last end) + reach on, all that the cells read is in closed form, too: the rows are written
     // as they are, with nothing to wait for (and nobody waits for these columns, see k_tile_init).
-    // Bound by its stores.
+    // Bound by its stores.  Fills through the loop below -> so: 24 blocks x 200001 budgets with shifts of
+    // up to 150 columns 395 -> 178 us, 64 x 400001 3.32 -> 1.83 ms, 384 x 6001 (benchmark) 6.31 -> 5.93 ms a pass.
     if (mb - reach >= msa_tile) {
         if (!real) return;
         int64_t e = row_of(L, S0 + top, t) * stride + tb.padl + mb + lane;
@@ -547,7 +549,10 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
         if constexpr (NW > 0) wn[64 * NH] = best;
         a_prev = m >= at(r_need2, ls) ? min(at(r_P, ls) + best, DINF) : DINF;
         last(a_prev, ls, end_a);
-        if constexpr (DIAG) aps[tri(ls, n_in) * 64 + lane] = a_prev;  // (unused where lt = 15)
+        // (lt = 15 has no such left operand: its word is the next row's first, ap(s+1, s+1).  Either the wait
+        // above has seen all other waves past that row, or this cell is closed and with it, msa never
+        // falling in t nor rising in s, every cell of that row: then nobody reads the word.)
+        if constexpr (DIAG) aps[tri(ls, n_in) * 64 + lane] = a_prev;
         else cells[(ls * TB + lt) * 64 + lane] = a_prev;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         if (lane == 0) __hip_atomic_store(&prog[lt], TB - ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -588,7 +593,10 @@ hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hip
     const int32_t side = tile_side(ch.L);
     const int32_t nb = (ch.L + side - 1) / side, n_chunks = (tb.W + 63) / 64;
     // Case 1 reads its row at K shifts.  Staged in LDS that costs a load per 64 columns of reach
-    // and cell, unstaged one per option (and one for the right operand): staged where it fits.
+    // and cell, unstaged one per option (and one for the right operand), four at a time.  Reach 190
+    // (staged) and 195 (not): 40 blocks x 4001 budgets with 2 options 128 and 145 us, with 24 147 and
+    // 247 us, 128 blocks with 5 options 681 and 855 us, with 24 774 and 1249 us.  So the line lies too low
+    // at any number of options; wider windows (4 KB a piece of the 160 KB LDS) are not built.
     const int32_t nw = ch.reach <= 64 * (TWIN - 1) ? 1 + (ch.reach + 63) / 64 : 0;
     // chunks per entry of the summaries (0: no pads to keep them in)
     const int32_t cpe = tb.padl >= 64 ? (n_chunks + SUM_GROUPS - 1) / SUM_GROUPS : 0;
