@@ -129,7 +129,7 @@ int geometry(const rk_chain *c, int32_t M, Geometry *g, size_t *bytes)
 // took 50-600 us where 20 do, its first schedule up to 0.6 ms longer).  A block given back is kept
 // for the next call, at most STAGES_KEPT of them until the process ends; set-up sees to the first.
 constexpr size_t STAGE_BYTES = (size_t)1 << 20;
-constexpr int STAGES_KEPT = 4;
+constexpr int STAGES_KEPT = 16;
 std::mutex g_stage_mu;
 void *g_stages[STAGES_KEPT];
 int g_n_stages = 0;

@@ -54,8 +54,8 @@ def test_rows_wider_than_a_block(M):
 
 
 def test_readers_in_several_threads():
-    """Ten threads, each with a chain of its own, read at the same time (more than the blocks kept)."""
-    chains = [make_random_chain(900 + k, 12 + k, 3, xmax=9, amax=20, tmax=9) for k in range(10)]
+    """Twenty threads, each with a chain of its own, read at the same time (more than the blocks kept)."""
+    chains = [make_random_chain(900 + k, 6 + k, 3, xmax=9, amax=20, tmax=9) for k in range(20)]
     want = [oracle.solve(c) for c in chains]
     bad = []
 
