@@ -9,18 +9,20 @@ the solve runs on a torch stream.
 
 Prints one JSON line on stdout.  ``value`` is DP relaxations per second of
 the whole step (relaxations = candidate evaluations of the recurrence,
-(M+1) * sum_d (L-d)(K+d)).  ``roofline`` reports the dominant fill kernel (the
-kind with the most device time, from HIP events the runtime records with each
-dispatch on the solve's stream) against the roof that binds it: HBM bandwidth for its compulsory table
-traffic (every row a launch reads counted once, plus the rows it writes) or the
-VALU integer peak for its relaxations (an add and a min each), whichever
-fraction is higher, both counting only what the kernels evaluate (a profiled step
-with the counting kernel variants reports the candidates and rows that the lower
-bound lets them skip); the other one is reported beside it; both are also priced
-against what this GPU sustains (``measured_ceilings``: int32 add/min chains over
-the whole chip, a 1 GiB device copy and a 1 GiB device read; a kernel's bandwidth ceiling
-is the time-weighted mix of the read rate and the write rate the copy implies, for its own
-share of bytes written).  ``cpu_baseline``
+(M+1) * sum_d (L-d)(K+d)).  ``roofline`` reports the timed fill, by square tiles of spans
+(``k_tile``, all but the first of its launches), from the HIP events around it on the solve's
+stream, against the VALU integer peak for every candidate of the recurrence (an add and a min each;
+the fill's bounds spare some, so this is the nominal rate) or HBM bandwidth for the three table rows
+that it writes per span, whichever fraction is higher; the other one is reported beside it, and its
+measured HBM traffic where the committed counter summary is current.  ``profiled_fill`` reports
+the fill by levels of diagonals, which profiled solves run (as chains with the saving
+sweep always do): the time of its kernels, and each kind of them (timed by HIP events the runtime records
+with each dispatch) against both roofs, counting only the candidates and table rows that the
+kernels evaluate (a profiled step with the counting kernel variants reports those that the lower
+bound lets them skip).  Both are also priced against what this GPU sustains
+(``measured_ceilings``: int32 add/min chains over the whole chip, a 1 GiB device copy and a 1 GiB
+device read; a fill's bandwidth ceiling is the time-weighted mix of the read rate and the write rate
+the copy implies, for its own share of bytes written).  ``cpu_baseline``
 times the CPU oracle (one core) on a bounded part of the same chain.  After
 the timed and profiled steps, ``tradeoff`` and ``option_pruning`` report the
 memory/time trade-off curve of the fill against Rotor's (Sec. 4) and the effect
@@ -68,17 +70,19 @@ def log(*a):
 
 def measured_traffic(workload: str, kernel: str):
     """HBM bytes per launch of `kernel` from the committed rocprofv3 counter summary,
-    if it was taken on the kernel source as it is now; else (None, None)."""
+    if it was taken on the kernel's source file as it is now; else (None, None)."""
     import hashlib
     path = os.path.join(ROOT, "profiles", f"hbm_traffic_{workload}.json")
     if not os.path.exists(path):
         return None, None
     with open(path) as f:
         prof = json.load(f)
-    with open(os.path.join(ROOT, prof["kernels_source"]), "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()
     k = prof["kernels"].get(kernel)
-    if sha != prof["kernels_source_sha256"] or k is None:
+    if k is None:
+        return None, None
+    with open(os.path.join(ROOT, k.get("source", prof["kernels_source"])), "rb") as f:
+        sha = hashlib.sha256(f.read()).hexdigest()
+    if sha != k.get("source_sha256", prof["kernels_source_sha256"]):
         return None, None
     return k["hbm_bytes_per_dispatch"], None
 
@@ -150,8 +154,7 @@ def extras(ch, s, M, oracle_rate=None):
     gs.close()
     log(f"option pruning: {pruning}")
 
-    # the smaller workloads: fill time (captured launch sequence replayed, median of 5 after
-    # one warm-up), launches and relaxations per second (launch latency bounds the small
+    # the smaller workloads: fill time (median of 5 after one warm-up), launches and relaxations per second (launch latency bounds the small
     # ones); the wall time of a synchronous solve (fill + answer) and of the schedule; the
     # oracle's time for the whole chain on one host core where it takes seconds, else
     # extrapolated from the oracle's measured rate on the benchmark sample
@@ -246,7 +249,7 @@ def main():
     log(f"workload {ch.name}: L={ch.L} K={ch.K} M={M} relaxations={relax:.3e} sha={ch.sha256()[:16]}")
 
     # cold solves (synchronous rk_solve on a fresh chain handle: upload, table allocation,
-    # capture of the launch sequence, fill).  The first one in the process also pays for the
+    # fill).  The first one in the process also pays for the
     # runtime loading the library's kernels; the second is what a new chain costs after that.
     cold_ms = {}
     for key in ("first_in_process", "new_chain_handle"):
@@ -271,8 +274,8 @@ def main():
         ans, nops = step()
         log(f"warmup {i}: answer={ans} ops={nops}")
 
-    # timed steps: the production path (the fill replays its captured launch sequence);
-    # HIP events around each fill on the solve's stream give the device fill time
+    # timed steps: the production path (the fill by tiles, its few launches straight to the
+    # stream); HIP events around each fill on the solve's stream give the device fill time
     fill_ms = []
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -282,10 +285,11 @@ def main():
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     ms_per_step = (t1 - t0) * 1e3 / args.steps
+    fill_launches = s.fill_ms()[1]
     log(f"timed {args.steps} steps: {ms_per_step:.3f} ms/step, fill median {statistics.median(fill_ms):.3f} ms")
 
-    # the same steps again with the kernels launched one by one, each dispatch recording a
-    # pair of HIP events at the kernel's start and end: per-kernel durations for the roofline
+    # the same solves by levels of diagonals (how profiled solves run), the kernels launched one by
+    # one, each dispatch recording a pair of HIP events at the kernel's start and end
     s.set_profiling(1)
     kern = {}
     for i in range(args.steps):
@@ -327,54 +331,57 @@ def main():
     if args.extras:  # other chains' fills: after the timed and profiled steps
         tradeoff, pruning, others, sweep = extras(ch, s, M, cpu["value"] if cpu else None)
 
-    # dominant kernel: the one with the most device time; both of its roofs per launch
-    dname, (dn, dms, _, dwork, dbytes) = max(kern.items(), key=lambda kv: kv[1][1])
-    per_launch_s = dms / dn * 1e-3
-    ops_per_launch = OPS_PER_RELAX * dwork / dn
-    bytes_per_launch = dbytes / dn
-    valu = {"bound": "alu", "achieved": ops_per_launch / per_launch_s / 1e12, "peak": VALU_PEAK_TOPS,
-            "unit": "TOP/s", "work_per_launch": ops_per_launch}
-    valu["frac"] = valu["achieved"] / VALU_PEAK_TOPS
-    hbm = {"bound": "hbm", "achieved": bytes_per_launch / per_launch_s / 1e9, "peak": HBM_PEAK_GBS,
-           "unit": "GB/s", "work_per_launch": bytes_per_launch}
-    hbm["frac"] = hbm["achieved"] / HBM_PEAK_GBS
-    bind, other = (hbm, valu) if hbm["frac"] >= valu["frac"] else (valu, hbm)
-    traffic, _ = measured_traffic(ch.name, dname)
+    # the timed fill against both roofs: every candidate of the recurrence, and the rows it writes
+    # (Opt and the two operand tables of the splits, once per span and budget)
+    fill_s = statistics.median(fill_ms) * 1e-3
+    written = 3 * 4 * ncells
+
+    def roof(bound, work, t_s):
+        peak, unit, scale = (VALU_PEAK_TOPS, "TOP/s", 1e12) if bound == "alu" else (HBM_PEAK_GBS, "GB/s", 1e9)
+        achieved = work / t_s / scale
+        return {"bound": bound, "achieved": achieved, "peak": peak, "unit": unit, "work": work, "frac": achieved / peak}
+
+    alu, hbm = roof("alu", OPS_PER_RELAX * relax, fill_s), roof("hbm", written, fill_s)
+    bind, other = (hbm, alu) if hbm["frac"] >= alu["frac"] else (alu, hbm)
+    tile_traffic, _ = measured_traffic(ch.name, "k_tile")  # bytes per launch
+    traffic = tile_traffic * (fill_launches - 1) if tile_traffic is not None else None
     roofline = dict(bind)
     roofline.update({
-        "traffic": traffic, "kernel": dname, "launches_per_step": dn / args.steps,
-        "avg_launch_ms": dms / dn, "other_roof": other,
-        "basis": "relaxations the kernel evaluates and table rows it reads: candidates of cells past "
-                 "the budget from which storing everything fits are written in closed form, and those "
-                 "that the lower bound lb(s,t) + P(s,i) rules out are skipped (counted on the device)",
+        "kernel": "k_tile", "fill_ms": fill_s * 1e3, "launches_per_step": fill_launches, "other_roof": other,
+        "traffic": traffic, "hbm_frac_measured": traffic / fill_s / 1e9 / HBM_PEAK_GBS if traffic is not None else None,
+        "basis": "the timed fill; alu: every candidate of the recurrence, of which the fill's bounds spare some; "
+                 "hbm: the table rows written, once (traffic: bytes per fill from counters)",
     })
-    # the whole fill against both roofs: every relaxation of the recurrence (nominal) and the
-    # ones the kernels evaluate, and the compulsory table traffic of all launches
-    fill_s = statistics.median(fill_ms) * 1e-3
+
+    # the profiled fill by diagonals: the time of its kernels (the events of each launch add to the
+    # gaps between them), and every kernel against both roofs, per launch, with its measured HBM
+    # traffic where the committed counter summary is current
+    diag_s = sum(v[1] for v in kern.values()) / args.steps * 1e-3
     evaluated = sum(v[3] for v in kern.values()) / args.steps
     table_bytes = sum(v[4] for v in kern.values()) / args.steps
-    # every fill kernel against both roofs (per launch, from the same profiled steps), with
-    # its measured HBM traffic per launch where the committed counter summary is current
-    roofline["per_kernel"] = {}
+    profiled = {
+        "fill": "by levels of diagonals", "kernels_ms": diag_s * 1e3,
+        "launches": sum(v[0] for v in kern.values()) / args.steps,
+        "relaxations_evaluated": evaluated, "table_bytes": table_bytes,
+        "valu_frac_evaluated": OPS_PER_RELAX * evaluated / diag_s / 1e12 / VALU_PEAK_TOPS,
+        "hbm_frac_compulsory": table_bytes / diag_s / 1e9 / HBM_PEAK_GBS,
+        "basis": "relaxations the kernels evaluate and table rows they read: candidates of cells past "
+                 "the budget from which storing everything fits are written in closed form, and those "
+                 "that the lower bound lb(s,t) + P(s,i) rules out are skipped (counted on the device)",
+        "per_kernel": {},
+    }
     for name, (n, ms, _, work, moved) in kern.items():
         if n == 0 or ms <= 0 or work == 0:
             continue
         t_s = ms / n * 1e-3
         meas, _ = measured_traffic(ch.name, name)
-        roofline["per_kernel"][name] = {
+        profiled["per_kernel"][name] = {
             "launches_per_step": n / args.steps, "avg_launch_ms": ms / n,
             "valu_frac": OPS_PER_RELAX * work / n / t_s / 1e12 / VALU_PEAK_TOPS,
             "hbm_frac_compulsory": moved / n / t_s / 1e9 / HBM_PEAK_GBS,
             "measured_bytes_per_launch": meas,
             "hbm_frac_measured": meas / t_s / 1e9 / HBM_PEAK_GBS if meas is not None else None,
         }
-    roofline["whole_fill"] = {
-        "fill_ms": fill_s * 1e3, "launches": sum(v[0] for v in kern.values()) / args.steps,
-        "relaxations_nominal": relax, "relaxations_evaluated": evaluated,
-        "valu_frac_nominal": OPS_PER_RELAX * relax / fill_s / 1e12 / VALU_PEAK_TOPS,
-        "valu_frac_evaluated": OPS_PER_RELAX * evaluated / fill_s / 1e12 / VALU_PEAK_TOPS,
-        "table_bytes": table_bytes, "hbm_frac_compulsory": table_bytes / fill_s / 1e9 / HBM_PEAK_GBS,
-    }
 
     # what this GPU sustains, next to the published peaks: int32 add+min chains over the
     # whole chip, a 1 GiB device copy (bytes read plus written) and a 1 GiB device read.
@@ -388,18 +395,19 @@ def main():
     inv_w = 2.0 / measured["copy_gbs"] - 1.0 / measured["read_gbs"]
     measured["write_gbs"] = 1.0 / inv_w if inv_w > 0 else None
     log(f"measured ceilings: {measured}")
-    wb = write_bytes_per_fill(dname, ch.L, M + 1)
-    write_share = wb / (dbytes / args.steps) if wb is not None and dbytes > 0 else None
+
+    def ceiling(write_share):
+        if write_share is None or not measured["write_gbs"]:
+            return measured["copy_gbs"]
+        return 1.0 / ((1.0 - write_share) / measured["read_gbs"] + write_share / measured["write_gbs"])
+
     for r in (roofline, roofline["other_roof"]):
-        if r["bound"] != "hbm":
-            r["measured_peak"] = measured["valu_int32_tops"]
-        elif write_share is not None and measured["write_gbs"]:
-            r["measured_peak"] = 1.0 / ((1.0 - write_share) / measured["read_gbs"]
-                                        + write_share / measured["write_gbs"])
-            r["write_share"] = write_share
-        else:
-            r["measured_peak"] = measured["copy_gbs"]
+        r["measured_peak"] = measured["valu_int32_tops"] if r["bound"] == "alu" else ceiling(1.0)
         r["frac_of_measured"] = r["achieved"] / r["measured_peak"]
+    for name, k in profiled["per_kernel"].items():
+        wb, moved = write_bytes_per_fill(name, ch.L, M + 1), kern[name][4] / args.steps
+        share = wb / moved if wb is not None and moved > 0 else None
+        k["hbm_frac_of_measured"] = k["hbm_frac_compulsory"] * HBM_PEAK_GBS / ceiling(share)
 
     out = {
         "metric": METRIC, "value": relax / (ms_per_step * 1e-3), "unit": "relaxations/s",
@@ -411,7 +419,7 @@ def main():
         "wall_solve_ms": statistics.median(wall), "cold_solve_ms": cold_ms, "fill_ms": statistics.median(fill_ms),
         "schedule_ms": sched_ms,
         "fill_relax_per_s": relax / (statistics.median(fill_ms) * 1e-3),
-        "roofline": roofline, "measured_ceilings": measured, "cpu_baseline": cpu, "tradeoff": tradeoff,
+        "roofline": roofline, "profiled_fill": profiled, "measured_ceilings": measured, "cpu_baseline": cpu, "tradeoff": tradeoff,
         "option_pruning": pruning, "other_workloads": others, "saving_sweep": sweep,
         "kernels": {k: {"launches_per_step": v[0] / args.steps, "ms_per_step": v[1] / args.steps,
                         "relaxations_per_step": v[2] // args.steps, "evaluated_per_step": v[3] // args.steps,
