@@ -1395,7 +1395,7 @@ __global__ __launch_bounds__(64 * AR_WAVES) void k_read_row(DevChain ch, Tables 
                                                             int32_t m0, int32_t n, int32_t *__restrict__ values,
                                                             int16_t *__restrict__ codes)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[2] = tiled ? *failed_at(tb) : 0;
+    const int32_t failed = tiled ? *failed_at(tb) : 0;  // (loaded beside the candidates, stored last)
     __shared__ uint64_t part[AR_WAVES][64];
     const int32_t lane = (int32_t)(threadIdx.x & 63), j = (int32_t)blockIdx.x * 64 + lane, mc = m0 + min(j, n - 1);
     const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
@@ -1419,6 +1419,7 @@ __global__ __launch_bounds__(64 * AR_WAVES) void k_read_row(DevChain ch, Tables 
         const int32_t v = opt_at(tb, ch.L, s, t, mc);
         values[j] = v >= DINF ? RK_INF : v;
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[2] = failed;
 }
 
 hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool tiled, int32_t m0, int32_t n,

@@ -107,10 +107,13 @@ __global__ __launch_bounds__(256) void k_tile_init(Tables tb, const int32_t *msa
 // index in LDS of the left operand ap(s, s + u), s = S0 + ls, u = 0 .. 14 - ls
 __device__ constexpr int32_t tri(int32_t ls, int32_t u) { return ls * (TB - 1) - ls * (ls - 1) / 2 + u; }
 
-template <bool DIAG, int NW>
-__global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_t level, int32_t side, int32_t n_chunks,
-                                                  int32_t reach, int32_t cpe, int32_t m_ans)
+// FULL: sides of TB blocks, as a constant (as an argument it costs more scalar registers than there
+// are: fill at 128 blocks x 2001 budgets 426 -> 432 us).
+template <bool DIAG, int NW, bool FULL>
+__global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_t level, int32_t side_arg, int32_t n_chunks,
+                                                  int32_t reach, int32_t flat_reach, int32_t cpe, int32_t m_ans)
 {
+    const int32_t side = FULL ? TB : side_arg;
     __shared__ __align__(16) int32_t cells[TB * TB * 64];  // the product's two staging buffers, then the tile
     __shared__ int32_t aps[(TRI + TB) * 64]; // left operands inside block S (reads run past a row's last)
     __shared__ int32_t win[NW ? TB * NW * 64 : 1];
@@ -190,11 +193,12 @@ __global__ __launch_bounds__(TB * 64) void k_tile(DevChain ch, Tables tb, int32_
     // From msa(S0, last end) + reach on, all that the cells read is in closed form, too: the rows are written
     // as they are, with nothing to wait for (and nobody waits for these columns, see k_tile_init).
     // Bound by its stores.  Fills through the loop below -> so: 24 blocks x 200001 budgets with shifts of
-    // up to 150 columns 395 -> 178 us, 64 x 400001 3.32 -> 1.83 ms, 384 x 6001 (benchmark) 6.31 -> 5.93 ms a pass.
-    if (mb - reach >= msa_tile) {
+    // up to 150 columns 395 -> 178 us, 64 x 400001 3.32 -> 1.83 ms, 384 x 6001 x 16 6.09 -> 5.72 ms.
+    if (mb - flat_reach >= msa_tile) {
         if (!real) return;
         int64_t e = row_of(L, S0 + top, t) * stride + tb.padl + mb + lane;
         int32_t lb = 0;
+#pragma unroll 1
         for (int32_t ls = top; ls >= 0; --ls) {
             lb = at(r_lb, ls);
             const bool only1 = (DIAG && ls == lt) || at(r_P1, ls) > 0;  // splits cost at least lb + r(F_s^0)
@@ -600,18 +604,23 @@ hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hip
     const int32_t nw = ch.reach <= 64 * (TWIN - 1) ? 1 + (ch.reach + 63) / 64 : 0;
     // chunks per entry of the summaries (0: no pads to keep them in)
     const int32_t cpe = tb.padl >= 64 ? (n_chunks + SUM_GROUPS - 1) / SUM_GROUPS : 0;
-    using Kernel = void (*)(DevChain, Tables, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t);
-    static const Kernel kernels[2][TWIN + 1] = {
-        {k_tile<false, 0>, k_tile<false, 1>, k_tile<false, 2>, k_tile<false, 3>, k_tile<false, 4>},
-        {k_tile<true, 0>, k_tile<true, 1>, k_tile<true, 2>, k_tile<true, 3>, k_tile<true, 4>}};
+    using Kernel = void (*)(DevChain, Tables, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t);
+    static const Kernel kernels[3][TWIN + 1] = {
+        {k_tile<true, 0, false>, k_tile<true, 1, false>, k_tile<true, 2, false>, k_tile<true, 3, false>, k_tile<true, 4, false>},
+        {k_tile<false, 0, false>, k_tile<false, 1, false>, k_tile<false, 2, false>, k_tile<false, 3, false>,
+         k_tile<false, 4, false>},
+        {k_tile<false, 0, true>, k_tile<false, 1, true>, k_tile<false, 2, true>, k_tile<false, 3, true>, k_tile<false, 4, true>}};
     static_assert(TWIN == 4, "one kernel per window width");
     hipLaunchKernelGGL(k_tile_init, dim3((uint32_t)n_rows(ch.L)), dim3(256), 0, stream, tb, ch.msa, ch.reach, nb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int32_t level = 0; level < nb; ++level) {
         const dim3 grid(chunk_grid(n_chunks, nb - level));
-        hipLaunchKernelGGL(kernels[level == 0][nw], grid, dim3(TB * 64), 0, stream, ch, tb, level, side, n_chunks,
-                           ch.reach, cpe, m_ans);
+        // tiles in closed form are left early where that lets other workgroups start; where all run at
+        // once their stores would only come first (128 blocks x 2001 budgets 423 -> 428 us with it)
+        const int32_t flat_reach = grid.x > 256 ? ch.reach : 1 << 30;
+        hipLaunchKernelGGL(kernels[level == 0 ? 0 : side < TB ? 1 : 2][nw], grid, dim3(TB * 64), 0, stream, ch, tb, level, side, n_chunks,
+                           ch.reach, flat_reach, cpe, m_ans);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     *launches = nb + 1;

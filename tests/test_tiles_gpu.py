@@ -47,19 +47,20 @@ def test_reach_of_case_1(reach):
     full_parity(ch, 900)
 
 
-@pytest.mark.parametrize("L,K,xmax,amax", [(1, 2, 4, 9), (16, 3, 0, 0), (17, 1, 3, 9), (33, 4, 30, 90), (40, 3, 60, 190), (100, 2, 2, 4)])
+@pytest.mark.parametrize("L,K,xmax,amax", [(1, 2, 4, 9), (16, 3, 0, 0), (17, 1, 3, 9), (33, 4, 30, 90), (40, 3, 60, 190), (50, 2, 2, 4)])
 def test_budgets_past_storing_everything(L, K, xmax, amax):
     """Columns where a tile and all that it reads are in closed form, next to ones where they are not:
-    budgets past storing everything, each span's own bound plus the largest shift among them."""
+    budgets past storing everything, each span's own bound plus the largest shift among them; launches of
+    up to 256 workgroups, which take the row loop there, too, and of more."""
     ch = make_random_chain(950 + L, L, K, xmax=max(xmax, 1), amax=max(amax, 1), tmax=7, tmin=0, allow_zero=True)
     if xmax == 0:
         ch.x[:], ch.mem[:] = 0, 0
     bound = store_all_bound(ch) + int((ch.x[1:, None] + ch.mem).max())
-    for M in (bound, bound + 64, bound + 133):
+    for M in (bound, bound + 64, bound + 133, bound + 64 * 256 + 1):
         full_parity(ch, M)
 
 
-@pytest.mark.parametrize("L,M,xmax,amax", [(16, 200, 70, 20), (21, 90, 9, 30), (33, 260, 30, 90), (36, 500, 90, 170), (20, 900, 5, 20)])
+@pytest.mark.parametrize("L,M,xmax,amax", [(16, 200, 70, 20), (21, 90, 9, 30), (33, 260, 30, 90), (36, 500, 90, 170), (20, 900, 5, 20), (20, 20000, 5, 20)])
 def test_operand_tables(L, M, xmax, amax):
     """The operands of the splits beside Opt: Opt(s, t, m - x_s), infinite for m < x_s, and
     P(s, t+1) + Opt(s, t, m), infinite where the sweep does not fit; staged and unstaged shifts."""
