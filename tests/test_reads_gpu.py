@@ -39,6 +39,32 @@ def test_first_reads_of_a_chain_cost_what_later_ones_do():
             s.close()
 
 
+def test_many_chains_alive_and_gone():
+    """1100 chains at once (more than one block of their pinned words), some destroyed and made again in
+    between: every answer and schedule is the chain's own."""
+    chains = [make_random_chain(60 + k, 2 + k, 2, xmax=5, amax=12, tmax=5) for k in range(10)]
+    want = [(sol.answer, oracle.schedule(sol)) for sol in map(oracle.solve, chains)]
+    solvers = []
+    try:
+        for k in range(1100):
+            s = rk.Solver(chains[k % 10])
+            assert s.solve() == want[k % 10][0]
+            solvers.append(s)
+            if k % 7 == 6:  # a chain in the middle goes, and comes back
+                j = (k * 31) % len(solvers)
+                solvers[j].close()
+                solvers[j] = rk.Solver(chains[j % 10])
+                assert solvers[j].solve() == want[j % 10][0]
+        for k, s in enumerate(solvers):
+            assert s.result() == want[k % 10][0], k
+            if k % 11 == 0:
+                ops, nf = s.schedule()
+                assert np.array_equal(ops, want[k % 10][1][0]) and nf == want[k % 10][1][1], k
+    finally:
+        for s in solvers:
+            s.close()
+
+
 @pytest.mark.parametrize("M", [174719, 174720, 262143, 262144, 400000])
 def test_rows_wider_than_a_block(M):
     """Rows of values and choices in pieces of 174720 columns, of values alone of 262144."""
