@@ -445,15 +445,16 @@ int read_row(rk_chain *c, int32_t s, int32_t t, int32_t n, int32_t *values, int1
     if (!stage.p) return RK_E_NOMEM;
     const int32_t piece = (int32_t)(STAGE_BYTES / (codes ? 6 : 4) / 64 * 64);
     const int32_t *const slot = c->run.opt.data() + (size_t)s * c->run.k_run;
+    const bool report = c->tiled && c->replayable;  // (else host[1] says it)
     for (int32_t m0 = 0; m0 < n; m0 += piece) {
         const int32_t k = std::min(n - m0, piece);
         int32_t *const v = static_cast<int32_t *>(stage.p);
         int16_t *const code = codes ? reinterpret_cast<int16_t *>(v + k) : nullptr;
         stage.idle = false;
-        HIPCHK(rk::launch_read_row(c->dc, c->tb, s, t, c->tiled, m0, k, v, code, c->own_stream));
+        HIPCHK(rk::launch_read_row(c->dc, c->tb, s, t, report, m0, k, v, code, c->own_stream));
         HIPCHK(hipStreamSynchronize(c->own_stream));
         stage.idle = true;
-        if (c->host[2]) return RK_E_INTERNAL;
+        if (c->tiled && c->host[report ? 2 : 1]) return RK_E_INTERNAL;
         if (values) std::copy(v, v + k, values + m0);
         for (int32_t m = 0; codes && m < k; ++m) {  // option slots back to the caller's option indices
             const int32_t w = code[m], o = w - c->h.L, o3 = o - c->run.k_run;

@@ -133,8 +133,8 @@ struct Tables {
     unsigned long long *ctr;
     int32_t *rec;
     // Pinned host memory that the tiled fill writes: [0] the answer Opt(0, L-1, M - x_0), [1]
-    // whether the fill failed (a wait that gave up); and that k_read_row writes: [2] whether the
-    // fill of the table it read failed.
+    // whether the fill failed (a wait that gave up); and that k_read_row writes when asked: [2]
+    // whether the fill of the table it read failed.
     int32_t *host;
 };
 
@@ -207,8 +207,8 @@ hipError_t launch_fill(const DevChain &ch, const Tables &tb, hipStream_t stream,
 bool tiles_pay(const DevChain &ch, int32_t W);
 hipError_t launch_tiles(const DevChain &ch, const Tables &tb, int32_t m_ans, hipStream_t stream, int32_t *launches);
 // Columns m0 .. m0 + n - 1 of row (s, t) as the ABI shows them (codes: choice codes in option slots,
-// or null); values and codes are pinned host memory.  tiled: the table's fill was a tiled one.
-hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool tiled, int32_t m0, int32_t n,
+// or null); values and codes are pinned host memory.  report: also whether the table's (tiled) fill failed.
+hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool report, int32_t m0, int32_t n,
                            int32_t *values, int16_t *codes, hipStream_t stream);
 // Alg. 3 on the device; ops and res are pinned host memory (ops past cap are counted, not
 // written); res[0] = number of steps, res[1] = index of the first

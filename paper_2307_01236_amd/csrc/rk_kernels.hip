@@ -1391,11 +1391,11 @@ __device__ inline uint64_t sweep_key(const DevChain &ch, const Tables &tb, int32
 // one thread per budget scanning them all took 35 us a row at 128 blocks x 2001 budgets, this
 // takes 5.8 us.
 constexpr int32_t AR_WAVES = 16;
-__global__ __launch_bounds__(64 * AR_WAVES) void k_read_row(DevChain ch, Tables tb, int32_t s, int32_t t, bool tiled,
+__global__ __launch_bounds__(64 * AR_WAVES) void k_read_row(DevChain ch, Tables tb, int32_t s, int32_t t, bool report,
                                                             int32_t m0, int32_t n, int32_t *__restrict__ values,
                                                             int16_t *__restrict__ codes)
 {
-    const int32_t failed = tiled ? *failed_at(tb) : 0;  // (loaded beside the candidates, stored last)
+    const int32_t failed = report ? *failed_at(tb) : 0;  // (loaded beside the candidates, stored last)
     __shared__ uint64_t part[AR_WAVES][64];
     const int32_t lane = (int32_t)(threadIdx.x & 63), j = (int32_t)blockIdx.x * 64 + lane, mc = m0 + min(j, n - 1);
     const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
@@ -1419,13 +1419,13 @@ __global__ __launch_bounds__(64 * AR_WAVES) void k_read_row(DevChain ch, Tables 
         const int32_t v = opt_at(tb, ch.L, s, t, mc);
         values[j] = v >= DINF ? RK_INF : v;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) tb.host[2] = failed;
+    if (report && blockIdx.x == 0 && threadIdx.x == 0) tb.host[2] = failed;
 }
 
-hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool tiled, int32_t m0, int32_t n,
+hipError_t launch_read_row(const DevChain &ch, const Tables &tb, int32_t s, int32_t t, bool report, int32_t m0, int32_t n,
                            int32_t *values, int16_t *codes, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_read_row, dim3((n + 63) / 64), dim3(codes ? 64 * AR_WAVES : 64), 0, stream, ch, tb, s, t, tiled,
+    hipLaunchKernelGGL(k_read_row, dim3((n + 63) / 64), dim3(codes ? 64 * AR_WAVES : 64), 0, stream, ch, tb, s, t, report,
                        m0, n, values, codes);
     return hipGetLastError();
 }

@@ -244,10 +244,11 @@ def test_very_wide_budgets_by_diagonals(L, first):
         cheap = cost[i] == cost[i].min()
         fits = min(max(int(n), int(x) + fits if i < L - 1 else 0) for n, x in zip(need[i][cheap], xbar[i][cheap]))
     assert fits > first
+    sols = {M: oracle.solve(ch, M) for M in (first - 1, first - 2)}
     s = rk.Solver(ch)
     try:
         for M in (first - 1, first - 2, first - 1, first - 1):  # M + 1 columns
-            sol = oracle.solve(ch, M)
+            sol = sols[M]
             assert s.solve(M) == sol.answer
             assert (s.fill_ms()[1] == 3) == (M + 1 < first)
             assert np.array_equal(s.tradeoff_curve(), oracle.tradeoff_curve(sol))
